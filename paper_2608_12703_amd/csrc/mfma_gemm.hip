@@ -26,7 +26,10 @@ namespace ad {
 
 constexpr int kNT = 128;          // output columns per workgroup (8 tiles of 16)
 
+// (no contraction into fused multiply-adds: every kernel rounds the same way, whatever the
+// code around it)
 __device__ __forceinline__ float gelu_erf(float v) {
+#pragma clang fp contract(off)
   return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
 }
 
@@ -572,6 +575,158 @@ __global__ void __launch_bounds__(512) lm_head_kernel(GemmArgs g) {
   }
 }
 
+// Operands of one 32-wide K step of a wave in the register-direct kernel: RTW row tiles
+// (hi / lo) and CTW column tiles.
+template <int RTW, int CTW>
+struct RStage {
+  uint4 w[CTW], h[RTW], l[RTW];
+};
+
+// Register-direct product for launches with few output tiles (reg_tile below): every wave
+// owns RTW row tiles x CTW 16-column tiles of one K split and works alone, with no LDS and no
+// barrier.  Both operands are stored in the matrix instruction's lane order, so each fragment
+// is one coalesced 1 KB load into registers, D K steps ahead.  A few rows leave
+// gemm_mfma_kernel 40-120 workgroups that each walk their K range at a barrier per step;
+// what bounds such a launch is the latency of that chain, and waves of one to eight tiles
+// spread it over the chip: one after another with a writer of the activations, weights from
+// HBM, 7 rows, d 1280: QKV 10.0 -> 3.9 us, d x d 5.9 -> 2.8, FFN-up 18.6 -> 6.2, FFN-down
+// 13.0 -> 5.5, the 51866-column LM head 37.6 -> 25.2 (5.3 TB/s of weights).  The order of
+// every output's sums is the same as in gemm_mfma_kernel.
+template <int EPI, int RTW, int CTW, int D, bool PACKED>
+__global__ void __launch_bounds__(256) gemm_reg_kernel(GemmArgs g) {
+  static_assert(EPI != EPI_ARGMAX || CTW == 4, "a top-2 record covers 64 columns");
+  constexpr bool kSw = EPI == EPI_GELU;
+  const int lane = threadIdx.x & 63, c16 = lane & 15, grp = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wpb = blockDim.x >> 6;
+  const int nwg = gridDim.x, bid = blockIdx.x;
+  const int x = bid & 7, q8 = nwg >> 3, r8 = nwg & 7;
+  const int lin = (x * q8 + min(x, r8) + (bid >> 3)) * wpb + w;
+  const int cgs = EPI == EPI_ARGMAX ? 2 * g.ntiles : (g.N + 16 * CTW - 1) / (16 * CTW);
+  const int mc = lin % g.mchunks, cg = (lin / g.mchunks) % cgs, s = lin / (g.mchunks * cgs);
+  if (s >= g.S) return;
+  const int rt0 = mc * RTW;
+  const int kb0 = (s * g.KB) / g.S, kb1 = ((s + 1) * g.KB) / g.S, kl = kb1 - 1, nk = kb1 - kb0;
+
+  const uint4* pa = (const uint4*)g.A + (size_t)rt0 * 128 + lane;
+  const uint4* pw[CTW];
+#pragma unroll
+  for (int ct = 0; ct < CTW; ++ct) {
+    const int t = min(cg * CTW + ct, g.ntiles * 8 - 1);   // 16-column tile
+    if constexpr (PACKED)
+      pw[ct] = (const uint4*)g.W + ((size_t)(t >> 3) * g.KB * 512 + (t & 7) * 64) + lane;
+    else
+      pw[ct] = (const uint4*)(g.W + (size_t)min(t * 16 + c16, g.N - 1) * g.K + grp * 8);
+  }
+  auto load = [&](RStage<RTW, CTW>& st, int kb) __attribute__((always_inline)) {
+    const int k = min(kb, kl);
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) st.w[ct] = pw[ct][(size_t)k * (PACKED ? 512 : 4)];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) {
+      st.h[r] = pa[((size_t)k * g.RT + r) * 128];
+      st.l[r] = pa[((size_t)k * g.RT + r) * 128 + 64];
+    }
+  };
+  f32x4 acc[RTW][CTW];
+#pragma unroll
+  for (int r = 0; r < RTW; ++r)
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) acc[r][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](const RStage<RTW, CTW>& st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+      for (int ct = 0; ct < CTW; ++ct) acc[r][ct] = mma_tile<kSw>(as_bf16x8(st.h[r]), as_bf16x8(st.w[ct]), acc[r][ct]);
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+      for (int ct = 0; ct < CTW; ++ct) acc[r][ct] = mma_tile<kSw>(as_bf16x8(st.l[r]), as_bf16x8(st.w[ct]), acc[r][ct]);
+  };
+  RStage<RTW, CTW> st[D];
+#pragma unroll
+  for (int u = 0; u < D; ++u) load(st[u], kb0 + u);
+  int kb = kb0;
+  for (int it = 0; it < (nk - 1) / D; ++it) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      mma(st[u]);
+      load(st[u], kb + D + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    kb += D;
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (kb + u < kb1) mma(st[u]);
+
+  const int row_base = rt0 * 16 + (kSw ? c16 : grp * 4);
+  const int col_base = cg * CTW * 16 + (kSw ? grp * 4 : c16);
+  if constexpr (EPI == EPI_ARGMAX) {
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = row_base + r * 16 + i;
+        Top2s t{-INFINITY, 0x7fffffff, -INFINITY, 0};
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) {
+          const int n = col_base + ct * 16;
+          const float v = acc[r][ct][i];
+          const bool fin = isfinite(v), in = n < g.N;
+          const Top2s u{(in & fin) ? v : -INFINITY, in ? n : 0x7fffffff, -INFINITY, (in & !fin) ? 1 : 0};
+          t = t2_merge(t, u);
+        }
+        t = t2_row16(t);
+        if (c16 == 0 && m < g.M) {
+          float4 rec{t.v1, __int_as_float(t.i1), t.v2, __int_as_float(t.bad)};
+          ((float4*)g.e.am_part)[(size_t)m * (2 * g.ntiles) + cg] = rec;
+        }
+      }
+    if (g.e.out) {
+#pragma unroll
+      for (int r = 0; r < RTW; ++r)
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int m = row_base + r * 16 + i, n = col_base + ct * 16;
+            if (m < g.M && n < g.N) g.e.out[(size_t)m * g.e.ldo + n] = acc[r][ct][i];
+          }
+    }
+  } else if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) {
+      const int n = col_base + ct * 16;
+      if (n >= g.N) continue;   // N is a multiple of 64: four columns are all in or all out
+      const uint2 bu = *(const uint2*)(g.bias + n);
+      const float b0 = bf16_to_f32(bu.x & 0xffff), b1 = bf16_to_f32(bu.x >> 16);
+      const float b2 = bf16_to_f32(bu.y & 0xffff), b3 = bf16_to_f32(bu.y >> 16);
+#pragma unroll
+      for (int r = 0; r < RTW; ++r) {
+        const int m = row_base + r * 16;
+        if (m >= g.M) continue;
+        afrag_store4(g.e.frag, g.e.frag_RT, m, n,
+                     float4{gelu_erf(acc[r][ct][0] + b0), gelu_erf(acc[r][ct][1] + b1),
+                            gelu_erf(acc[r][ct][2] + b2), gelu_erf(acc[r][ct][3] + b3)});
+      }
+    }
+  } else {
+    float* P = g.part + (size_t)s * g.M * g.N;
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = row_base + r * 16 + i;
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) {
+          const int n = col_base + ct * 16;
+          if (n < g.N) __builtin_nontemporal_store(acc[r][ct][i], &P[(size_t)m * g.N + n]);
+        }
+      }
+  }
+}
+
 // Tiled weight copy (see launch.h): one thread per 16-byte piece.
 __global__ void __launch_bounds__(256) pack_weight_kernel(const uint16_t* W, int N, int K,
                                                           uint16_t* P, size_t pieces) {
@@ -689,8 +844,64 @@ static void launch_rtc(const GemmArgs& g, dim3 grid, hipStream_t st) {
     hipLaunchKernelGGL((gemm_mfma_kernel<EPI, RTC, PACKED, false, kWide>), grid, dim3(512), 0, st, g);
 }
 
+// Tile of the register-direct kernel for a launch of `tiles` 16 x 16 output tiles (row tiles
+// x column tiles x splits), or none (rtw 0): gemm_mfma_kernel.  More tiles per wave save
+// operand bytes (a wave loads 2 RTW + CTW KB for RTW CTW products of a K step, and a CU's
+// vector cache delivers 64 bytes a clock), fewer spread the launch over more waves; the
+// lines lie where the measured times cross (chain of writer and product, us, d 1280; tiles
+// in brackets): 32 rows, FFN-up [640] 1x1 7.2, 1x2 8.1; QKV [960] 1x1 5.7, 1x2 5.0; 64 rows,
+// d x d [1600] 1x2 3.9, 1x4 3.9; QKV [1920] 1x2 6.6, 1x4 6.1; 80 rows, QKV [2400] 1x4 8.6,
+// 2x4 8.0; 112 rows, FFN-down [3360] 1x4 13.3, 2x4 10.4, LDS kernel 13.0; 160 rows, d x d
+// [4000] 2x4 5.3, LDS 6.3; QKV [4800] 2x4 10.6, LDS 10.4.
+struct RegTile {
+  int rtw, ctw;
+};
+static RegTile reg_tile(int epi, int MT, int N, int S) {
+  if (epi == EPI_ARGMAX) {
+    // 64 columns per wave (a top-2 record); 51866 columns, register-direct against LDS: 1 row
+    // tile 25.2 / 37.6 us, 2 28.5 / 37.8, 3 34.0 / 38.1, 4 39.6 / 38.0 (one chunk of four
+    // row tiles is the LDS kernel's best case), 5 47.9 / 63.0, 7 62.2 / 64.4, 10 73 / 64
+    if (MT <= 3) return {MT, 4};
+    return {MT == 5 || MT == 6 ? 3 : 0, 4};
+  }
+  const long long tiles = (long long)MT * ((N + 15) / 16) * S;
+  if (tiles <= 720) return {1, 1};
+  if (tiles <= 1700) return {1, 2};
+  if (tiles <= 2300) return {1, 4};
+  return {tiles <= 4000 ? 2 : 0, 4};
+}
+
+// waves: waves per workgroup (they take neighbouring tiles)
+template <int EPI, int RTW, int CTW, int D>
+static void launch_reg(GemmArgs g, int waves, hipStream_t st) {
+  g.mchunks = ((g.M + 15) / 16 + RTW - 1) / RTW;
+  const int cgs = EPI == EPI_ARGMAX ? 2 * g.ntiles : (g.N + 16 * CTW - 1) / (16 * CTW);
+  const dim3 grid((g.mchunks * cgs * g.S + waves - 1) / waves), block(64 * waves);
+  if (g.packed) hipLaunchKernelGGL((gemm_reg_kernel<EPI, RTW, CTW, D, true>), grid, block, 0, st, g);
+  else hipLaunchKernelGGL((gemm_reg_kernel<EPI, RTW, CTW, D, false>), grid, block, 0, st, g);
+}
+
+template <int EPI>
+static bool launch_reg_any(const GemmArgs& g, hipStream_t st) {
+  const RegTile t = reg_tile(EPI, (g.M + 15) / 16, g.N, g.S);
+  if constexpr (EPI == EPI_ARGMAX) {
+    if (t.rtw == 1) launch_reg<EPI, 1, 4, 8>(g, 4, st);
+    else if (t.rtw == 2) launch_reg<EPI, 2, 4, 5>(g, 4, st);
+    else if (t.rtw == 3) launch_reg<EPI, 3, 4, 4>(g, 1, st);
+    else return false;
+  } else {
+    if (t.rtw == 2) launch_reg<EPI, 2, 4, 4>(g, 2, st);
+    else if (t.rtw == 0) return false;
+    else if (t.ctw == 1) launch_reg<EPI, 1, 1, 8>(g, 2, st);
+    else if (t.ctw == 2) launch_reg<EPI, 1, 2, 8>(g, 2, st);
+    else launch_reg<EPI, 1, 4, 6>(g, 2, st);
+  }
+  return true;
+}
+
 template <int EPI>
 static void launch_one(GemmArgs g, hipStream_t st) {
+  if (launch_reg_any<EPI>(g, st)) return;
   const int rtc = gemm_rtc(g.M, g.N, g.S);
   g.mchunks = mchunks_of(g.M, rtc);
   if (EPI == EPI_ARGMAX && rtc == 16 && g.ntiles * g.mchunks > kMaxWGs &&
