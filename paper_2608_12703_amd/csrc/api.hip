@@ -884,29 +884,36 @@ ad_status ad_cross_kv_prefill(const ad_model* model, const void* enc, const ad_c
   // order, staged in the last layer's part of the cache (frames_cap x 2d elements, at
   // least the frames_cap x d of the copy), which is only written by the last launch;
   // that launch reads the row-major states.  A tiled model supplies tiled weights.
-  const bool stage = D.dtype == AD_BF16 && D.n_layers >= 2;
-  const size_t layer_elems = (size_t)2 * D.n_heads * cross->frames_cap * 64;
-  uint16_t* staged = (uint16_t*)cross->data + (size_t)(D.n_layers - 1) * layer_elems;
-  if (stage) {
-    const uintptr_t e0 = (uintptr_t)enc, e1 = e0 + (size_t)cross->frames_cap * D.d_model * 2;
-    const uintptr_t s0 = (uintptr_t)staged, s1 = s0 + layer_elems * 2;
-    if (e0 < s1 && s0 < e1) return fail(AD_EINVAL, "enc overlaps the last layer's cross-K/V slots");
-  }
-  if (stage) ad::launch_pack_rows((const uint16_t*)enc, cross->frames_cap, D.d_model, staged, st);
-  for (int l = 0; l < D.n_layers; ++l) {
-    e.layer = l;
-    if (D.dtype == AD_BF16) {
-      const bool a_packed = stage && l < D.n_layers - 1;
-      const bool w_packed = model->packed != nullptr;
-      const uint16_t* W = w_packed ? model->packed + model->pack_off[l * kPackedPerLayer + kPackedXkv]
-                                   : (const uint16_t*)lp(model, l, W_XKV);
-      ad::launch_xkv_mfma(cross->frames_cap, 2 * D.d_model, D.d_model,
-                          a_packed ? staged : (const uint16_t*)enc, a_packed, W, w_packed,
-                          (const uint16_t*)lp(model, l, B_XKV), (uint16_t*)cross->data, l, D.n_heads,
-                          D.d_model, cross->frames_cap, st);
-    } else
+  if (D.dtype == AD_BF16) {
+    const bool packed = model->packed != nullptr;
+    const int staged_layers = D.n_layers - 1;
+    uint16_t* staged = (uint16_t*)cross->data + (size_t)staged_layers * 2 * D.n_heads * cross->frames_cap * 64;
+    auto project = [&](int l0, int n, const uint16_t* A, bool a_packed) {
+      ad::XkvLayers lay{};
+      lay.first = l0;
+      for (int i = 0; i < n; ++i) {
+        lay.W[i] = packed ? model->packed + model->pack_off[(l0 + i) * kPackedPerLayer + kPackedXkv]
+                          : (const uint16_t*)lp(model, l0 + i, W_XKV);
+        lay.bias[i] = (const uint16_t*)lp(model, l0 + i, B_XKV);
+      }
+      ad::launch_xkv_mfma(cross->frames_cap, 2 * D.d_model, D.d_model, A, a_packed, lay, n, packed,
+                          (uint16_t*)cross->data, D.n_heads, D.d_model, cross->frames_cap, st);
+    };
+    if (staged_layers > 0) {
+      const uintptr_t e0 = (uintptr_t)enc, e1 = e0 + (size_t)cross->frames_cap * D.d_model * 2;
+      const uintptr_t s0 = (uintptr_t)staged, s1 = s0 + (size_t)4 * D.n_heads * cross->frames_cap * 64;
+      if (e0 < s1 && s0 < e1) return fail(AD_EINVAL, "enc overlaps the last layer's cross-K/V slots");
+      ad::launch_pack_rows((const uint16_t*)enc, cross->frames_cap, D.d_model, staged, st);
+    }
+    for (int l0 = 0; l0 < staged_layers; l0 += ad::kXkvLayers)
+      project(l0, std::min(ad::kXkvLayers, staged_layers - l0), staged, true);
+    project(staged_layers, 1, (const uint16_t*)enc, false);
+  } else {
+    for (int l = 0; l < D.n_layers; ++l) {
+      e.layer = l;
       ad::launch_gemm_valu<ad::F32>(ad::EPI_XKV, cross->frames_cap, 2 * D.d_model, D.d_model,
                                     (const float*)enc, lp(model, l, W_XKV), lp(model, l, B_XKV), e, st);
+    }
   }
   return check_hip("ad_cross_kv_prefill");
 }

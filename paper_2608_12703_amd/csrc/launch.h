@@ -88,13 +88,19 @@ template <class S>
 void launch_gemm_valu(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
                       const EpiArgs& e, hipStream_t st);
 
-// Cross-attention keys / values of a bf16 model's encoder states on the matrix cores:
-// cache <- enc [M][K] W [N][K]^T + bias in the cross-K/V layout of `layer` (N = 2d, M a
-// multiple of 32).  a_packed: enc as written by launch_pack_rows; w_packed: W tiled by
-// launch_pack_weight; otherwise row-major.
-void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const uint16_t* W,
-                     bool w_packed, const uint16_t* bias, uint16_t* cache, int layer, int H, int d,
-                     int frames_cap, hipStream_t st);
+// Cross-attention keys / values of a bf16 model's encoder states on the matrix cores, for
+// `layers` consecutive layers (at most kXkvLayers): cache <- enc A [M][K] W[i] [N][K]^T +
+// bias[i] in the cross-K/V layout of layer first + i (N = 2d, M a multiple of 32).  a_packed:
+// enc as written by launch_pack_rows; w_packed: W tiled by launch_pack_weight; otherwise
+// row-major.
+constexpr int kXkvLayers = 64;   // layers of one launch (1 KB of kernel arguments)
+struct XkvLayers {
+  const uint16_t* W[kXkvLayers];
+  const uint16_t* bias[kXkvLayers];
+  int first;
+};
+void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const XkvLayers& lay, int layers,
+                     bool w_packed, uint16_t* cache, int H, int d, int frames_cap, hipStream_t st);
 // Row-major bf16 [M][K] (M a multiple of 16, K of 32) into the fragment order the
 // prefill reads (M * K elements).
 void launch_pack_rows(const uint16_t* A, int M, int K, uint16_t* P, hipStream_t st);
