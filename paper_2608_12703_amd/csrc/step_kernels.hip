@@ -507,14 +507,11 @@ __global__ void kv_copy_kernel(int L, int H, int n, int b, typename S::T* lin,
 // token-major in a tile, so their pieces move as they are, in the cache's order (128-byte runs
 // of the linear array).  Values are lane-major and are transposed through LDS.  Bound by
 // memory; the element-wise kernel spent its time on index divisions and 2-byte accesses.
-// 220 tokens of the large-v3 cache, 36 MB each way, import and export 54 + 50 us ->
-// 20.5 + 20.5 us (3.5 TB/s).
+// 220 tokens of the large-v3 cache, 36 MB each way: import and export 125 -> 27 us together
+// (5.4 TB/s); 53 tokens of 30 layers x 4 heads 6.2 + 4.9 -> 3.4 + 2.9 us.
+// (Loads are unconditional, tokens and heads past the tile clamped, so that all of a thread's
+// are in flight together.)
 constexpr int kCopyHeads = 4;
-template <class T>
-struct alignas(16) Piece {
-  static constexpr int E = 16 / sizeof(T);
-  T v[E];
-};
 
 template <class S, bool EXPORT>
 __global__ void __launch_bounds__(256) kv_copy_tile_kernel(int H, int n, int b, typename S::T* lin,
@@ -522,72 +519,74 @@ __global__ void __launch_bounds__(256) kv_copy_tile_kernel(int H, int n, int b, 
                                                            const int* block_table, int pages_per_seq,
                                                            int* err) {
   using T = typename S::T;
-  using P = Piece<T>;
-  constexpr int E = P::E, kRow = kCopyHeads * kHead, kPieces = kTile * kRow / E;
+  constexpr int E = 16 / sizeof(T), kRow = kCopyHeads * kHead, kPer = kTile * kRow / E / 256;
+  typedef T P __attribute__((ext_vector_type(E)));
   __shared__ __align__(16) T tr[kTile][kRow + E];   // values: [token][head, lane]
   const int tile = blockIdx.x, layer = blockIdx.y >> 1, kv = blockIdx.y & 1, h0 = blockIdx.z * kCopyHeads;
   const int pg = block_table[(size_t)b * pages_per_seq + tile];
+  const int cnt = min(kTile, n - tile * kTile);          // tokens of this tile
+  const int cols = min(kCopyHeads, H - h0) * kHead;      // lanes of these heads
+  const size_t row = (size_t)H * kHead;
+  T* lp = lin + ((size_t)blockIdx.y * n + (size_t)tile * kTile) * row + h0 * kHead;
+  // piece i of this thread: element q; keys in the cache's order (head, token, lane), values
+  // in the linear order (token, head and lane)
+  int t[kPer], c[kPer], q[kPer];
+  bool on[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    q[i] = (threadIdx.x + 256 * i) * E;
+    t[i] = kv == 0 ? q[i] % kTileElems / kHead : q[i] / kRow;
+    c[i] = kv == 0 ? q[i] / kTileElems * kHead + q[i] % kHead : q[i] % kRow;
+    on[i] = t[i] < cnt && c[i] < cols;
+  }
+  P v[kPer];
+  if (!EXPORT) {   // (the linear side does not wait for the page)
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) v[i] = *(const P*)(lp + min(t[i], cnt - 1) * row + (on[i] ? c[i] : 0));
+  }
   if (pg < 0 || pg >= num_pages) {
     if (threadIdx.x == 0) atomicOr(err, 2);
     return;
   }
-  const int cnt = min(kTile, n - tile * kTile);   // tokens of this tile
-  const int nh = min(kCopyHeads, H - h0);
-  const size_t row = (size_t)H * kHead;
-  T* lp = lin + ((size_t)blockIdx.y * n + (size_t)tile * kTile) * row + h0 * kHead;
   T* pp = pool + kv_tile_base(layer, kv, pg, h0, num_pages, H);
-  // this thread's pieces in the cache's order: element o of head h, and the token and lane of
-  // its first element
-  constexpr int kPer = kPieces / 256;
+  if (EXPORT) {   // the cache's order on both paths
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) v[i] = *(const P*)(pp + (q[i] < cols * kTile ? q[i] : 0));
+  }
   if (kv == 0) {
-    P v[kPer];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, h = q / kTileElems, t = q % kTileElems / kHead, j = q % kHead;
-      if (h < nh && t < cnt) v[i] = EXPORT ? *(const P*)(pp + q) : *(const P*)(lp + t * row + h * kHead + j);
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, h = q / kTileElems, t = q % kTileElems / kHead, j = q % kHead;
-      if (h < nh && t < cnt) *(P*)(EXPORT ? lp + t * row + h * kHead + j : pp + q) = v[i];
-    }
+    for (int i = 0; i < kPer; ++i)
+      if (on[i]) *(P*)(EXPORT ? lp + t[i] * row + c[i] : pp + q[i]) = v[i];
     return;
   }
-  // one side in the linear order (token, lanes), the other in the cache's (lane, tokens)
-  if (!EXPORT) {
+  // values in the cache's order: elements q .. q + E - 1 are tokens tv .. of lane cv
+  if (EXPORT) {
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, t = q / kRow, c = q % kRow;
-      if (c < nh * kHead && t < cnt) *(P*)&tr[t][c] = *(const P*)(lp + t * row + c);
-    }
+    for (int i = 0; i < kPer; ++i)
+#pragma unroll
+      for (int u = 0; u < E; ++u) tr[q[i] % kTile + u][q[i] / kTile] = v[i][u];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, c = q / kTile, t = q % kTile;
-      if (c >= nh * kHead || t >= cnt) continue;
-      P o;
+    for (int i = 0; i < kPer; ++i)
+      if (on[i]) *(P*)(lp + t[i] * row + c[i]) = *(const P*)&tr[t[i]][c[i]];
+    return;
+  }
 #pragma unroll
-      for (int u = 0; u < E; ++u) o.v[u] = tr[t + u][c];
-      if (t + E <= cnt) {
-        *(P*)(pp + q) = o;
-      } else {   // the tokens past n keep what their slots hold
-        for (int u = 0; t + u < cnt; ++u) pp[q + u] = tr[t + u][c];
-      }
-    }
-  } else {
+  for (int i = 0; i < kPer; ++i) *(P*)&tr[t[i]][c[i]] = v[i];
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, c = q / kTile, t = q % kTile;
-      if (c >= nh * kHead || t >= cnt) continue;
-      const P o = *(const P*)(pp + q);
+  for (int i = 0; i < kPer; ++i) {
+    const int cv = q[i] / kTile, tv = q[i] % kTile;
+    if (cv >= cols || tv >= cnt) continue;
+    P o;
 #pragma unroll
-      for (int u = 0; u < E; ++u) tr[t + u][c] = o.v[u];
-    }
-    __syncthreads();
+    for (int u = 0; u < E; ++u) o[u] = tr[tv + u][cv];
+    if (tv + E <= cnt) {
+      *(P*)(pp + q[i]) = o;
+    } else {   // the tokens past n keep what their slots hold
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int q = (threadIdx.x + 256 * i) * E, t = q / kRow, c = q % kRow;
-      if (c < nh * kHead && t < cnt) *(P*)(lp + t * row + c) = *(const P*)&tr[t][c];
+      for (int u = 0; u < E; ++u)
+        if (tv + u < cnt) pp[q[i] + u] = o[u];
     }
   }
 }
