@@ -224,7 +224,7 @@ void accept(const ad_step* s, const Workspace& w, const int* greedy, hipStream_t
 }
 
 template <class S>
-void run_step_valu(const ad_model* m, const ad_step* s, const Workspace& w, hipStream_t st) {
+void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipStream_t st) {
   const ad_model_desc& D = m->desc;
   const int M = s->rows, d = D.d_model, F = D.d_ffn, H = D.n_heads, V = D.vocab;
   ad::StepArgs a{s->batch, s->layout, s->k_max, s->rows, V, D.max_pos, D.max_frames,
@@ -247,7 +247,7 @@ void run_step_valu(const ad_model* m, const ad_step* s, const Workspace& w, hipS
     // self-attention sublayer
     ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN1_G), lp(m, l, LN1_B), w.ln, st);
     e.out = w.q; e.ldo = d; e.cache = s->kv.pool;
-    ad::launch_gemm_valu<S>(ad::EPI_QKV, M, 3 * d, d, w.ln, lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_QKV, M, 3 * d, d, w.ln, lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
     {
       ProfScope ps(m, AD_PROF_SELF_ATTN, st);
       ad::launch_self_attn_valu<S>(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gself, w.att,
@@ -255,11 +255,11 @@ void run_step_valu(const ad_model* m, const ad_step* s, const Workspace& w, hipS
                                    w.tree, st);
     }
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_valu<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_O), lp(m, l, B_O), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_O), lp(m, l, B_O), e, st);
     // cross-attention sublayer
     ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN2_G), lp(m, l, LN2_B), w.ln, st);
     e.out = w.q; e.ldo = d;
-    ad::launch_gemm_valu<S>(ad::EPI_STORE, M, d, d, w.ln, lp(m, l, W_XQ), lp(m, l, B_XQ), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_STORE, M, d, d, w.ln, lp(m, l, W_XQ), lp(m, l, B_XQ), e, st);
     if (l == s->anchor_layer) {
       (void)hipMemcpyAsync(w.q_anchor, w.q, sizeof(float) * M * d, hipMemcpyDeviceToDevice, st);
       if (s->out_xq)
@@ -271,13 +271,13 @@ void run_step_valu(const ad_model* m, const ad_step* s, const Workspace& w, hipS
                                     s->cross.data, s->cross.frames_cap, st);
     }
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_valu<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_XO), lp(m, l, B_XO), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_XO), lp(m, l, B_XO), e, st);
     // feed-forward sublayer
     ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN3_G), lp(m, l, LN3_B), w.ln, st);
     e.out = w.hid; e.ldo = F;
-    ad::launch_gemm_valu<S>(ad::EPI_GELU, M, F, d, w.ln, lp(m, l, W_1), lp(m, l, B_1), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_GELU, M, F, d, w.ln, lp(m, l, W_1), lp(m, l, B_1), e, st);
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_valu<S>(ad::EPI_RESID, M, d, F, w.hid, lp(m, l, W_2), lp(m, l, B_2), e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, F, w.hid, lp(m, l, W_2), lp(m, l, B_2), e, st);
     copy_taps(s, l, w.x, M, d, st);
   }
   float* hidden = s->out_hidden ? s->out_hidden : w.hidden;
@@ -286,7 +286,7 @@ void run_step_valu(const ad_model* m, const ad_step* s, const Workspace& w, hipS
   e.out = logits; e.ldo = V;
   {
     ProfScope ps(m, AD_PROF_LM_HEAD, st);
-    ad::launch_gemm_valu<S>(ad::EPI_STORE, M, V, d, hidden, m->p[P_TOK], nullptr, e, st);
+    ad::launch_gemm_f32<S>(ad::EPI_STORE, M, V, d, hidden, m->p[P_TOK], nullptr, e, st);
   }
   int* greedy = s->out_greedy ? s->out_greedy : w.greedy;
   ad::launch_argmax(M, V, logits, V, w.rows, greedy, s->out_margin, s->err_flag, st);
@@ -624,7 +624,7 @@ ad_status ad_verify_step(const ad_model* model, const ad_step* s, void* stream) 
   const Workspace w = carve(D, s->rows, s->batch, s->k_max, (char*)s->workspace);
   hipStream_t st = (hipStream_t)stream;
   if (D.dtype == AD_BF16) run_step_mfma(model, s, w, st);
-  else run_step_valu<ad::F32>(model, s, w, st);
+  else run_step_f32<ad::F32>(model, s, w, st);
   return check_hip("ad_verify_step");
 }
 
@@ -744,14 +744,14 @@ ad_status ad_draft_input(const ad_model* model, const void* w_fuse, const void* 
     ad::launch_draft_gather_taps(batch, d, layout, k_max, cu_rows, accept_len, rows, taps, hidden,
                                  taps4, st);
     e.out = feat;
-    if (bf16) ad::launch_gemm_valu<ad::BF16>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
-    else ad::launch_gemm_valu<ad::F32>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
+    if (bf16) ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
+    else ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
     f = feat;
   }
   ad::launch_draft_concat(batch, d, f, model->p[P_TOK], bf16, tokens, token_stride, token_index, z, st);
   e.out = out;
-  if (bf16) ad::launch_gemm_valu<ad::BF16>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
-  else ad::launch_gemm_valu<ad::F32>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
+  if (bf16) ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
+  else ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
   if (anchor) ad::launch_draft_window(batch, anchor, enc_len, half_window, window, st);
   return check_hip("ad_draft_input");
 }
@@ -879,23 +879,27 @@ ad_status ad_cross_kv_prefill(const ad_model* model, const void* enc, const ad_c
   e.H = D.n_heads;
   e.d = D.d_model;
   e.frames_cap = cross->frames_cap;
-  // bf16 models: the matrix cores (a large dense product); float32 models: the VALU.
+  // layers l0 .. l0 + n - 1 of one launch; a tiled model supplies tiled weights
+  const bool packed = model->packed != nullptr;
+  auto layers = [&](int l0, int n) {
+    ad::XkvLayers lay{};
+    lay.first = l0;
+    for (int i = 0; i < n; ++i) {
+      lay.W[i] = packed ? model->packed + model->pack_off[(l0 + i) * kPackedPerLayer + kPackedXkv]
+                        : lp(model, l0 + i, W_XKV);
+      lay.bias[i] = lp(model, l0 + i, B_XKV);
+    }
+    return lay;
+  };
   // With two or more layers the bf16 path first copies the encoder states into fragment
   // order, staged in the last layer's part of the cache (frames_cap x 2d elements, at
   // least the frames_cap x d of the copy), which is only written by the last launch;
-  // that launch reads the row-major states.  A tiled model supplies tiled weights.
+  // that launch reads the row-major states.
   if (D.dtype == AD_BF16) {
-    const bool packed = model->packed != nullptr;
     const int staged_layers = D.n_layers - 1;
     uint16_t* staged = (uint16_t*)cross->data + (size_t)staged_layers * 2 * D.n_heads * cross->frames_cap * 64;
     auto project = [&](int l0, int n, const uint16_t* A, bool a_packed) {
-      ad::XkvLayers lay{};
-      lay.first = l0;
-      for (int i = 0; i < n; ++i) {
-        lay.W[i] = packed ? model->packed + model->pack_off[(l0 + i) * kPackedPerLayer + kPackedXkv]
-                          : (const uint16_t*)lp(model, l0 + i, W_XKV);
-        lay.bias[i] = (const uint16_t*)lp(model, l0 + i, B_XKV);
-      }
+      const ad::XkvLayers lay = layers(l0, n);
       ad::launch_xkv_mfma(cross->frames_cap, 2 * D.d_model, D.d_model, A, a_packed, lay, n, packed,
                           (uint16_t*)cross->data, D.n_heads, D.d_model, cross->frames_cap, st);
     };
@@ -909,10 +913,9 @@ ad_status ad_cross_kv_prefill(const ad_model* model, const void* enc, const ad_c
       project(l0, std::min(ad::kXkvLayers, staged_layers - l0), staged, true);
     project(staged_layers, 1, (const uint16_t*)enc, false);
   } else {
-    for (int l = 0; l < D.n_layers; ++l) {
-      e.layer = l;
-      ad::launch_gemm_valu<ad::F32>(ad::EPI_XKV, cross->frames_cap, 2 * D.d_model, D.d_model,
-                                    (const float*)enc, lp(model, l, W_XKV), lp(model, l, B_XKV), e, st);
+    for (int l0 = 0; l0 < D.n_layers; l0 += ad::kXkvLayers) {
+      const int n = std::min(ad::kXkvLayers, D.n_layers - l0);
+      ad::launch_xkv_f32(cross->frames_cap, 2 * D.d_model, D.d_model, (const float*)enc, layers(l0, n), n, e, st);
     }
   }
   return check_hip("ad_cross_kv_prefill");
@@ -958,9 +961,9 @@ ad_status ad_draft_heads(const ad_model* model, const void* heads_w, int32_t n_h
     e.ldo = D.vocab;
     const void* w = (const char*)heads_w + (size_t)i * D.vocab * D.d_model * esz;
     if (D.dtype == AD_BF16)
-      ad::launch_gemm_valu<ad::BF16>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
+      ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
     else
-      ad::launch_gemm_valu<ad::F32>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
+      ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
   }
   // the err flag of the step is not touched here: non-finite head logits give -1 drafts
   ad::launch_argmax(n_heads * batch, D.vocab, logits, D.vocab, nullptr, greedy, nullptr, nullptr, st);

@@ -83,9 +83,10 @@ void launch_gather_hidden(int B, int d, int layout, int k_max, const int* cu_row
 void launch_assemble_next(int B, int n_heads, int k_max, const int* accept_len, const int* out_tokens,
                           const int* head_greedy, int* next_tokens, hipStream_t st);
 
-// C = A W^T (+ bias) with the epilogue `epi`; A is float32 [M][K], W is [N][K] of S.
+// C = A W^T (+ bias) in float32 with the epilogue `epi` (EPI_STORE, and for float32 weights
+// EPI_RESID, EPI_GELU, EPI_QKV); A is float32 [M][K], W is [N][K] of S.
 template <class S>
-void launch_gemm_valu(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
+void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
                       const EpiArgs& e, hipStream_t st);
 
 // Cross-attention keys / values of a bf16 model's encoder states on the matrix cores, for
@@ -95,12 +96,15 @@ void launch_gemm_valu(int epi, int M, int N, int K, const float* A, const void* 
 // row-major.
 constexpr int kXkvLayers = 64;   // layers of one launch (1 KB of kernel arguments)
 struct XkvLayers {
-  const uint16_t* W[kXkvLayers];
-  const uint16_t* bias[kXkvLayers];
+  const void* W[kXkvLayers];      // of the model's type
+  const void* bias[kXkvLayers];
   int first;
 };
 void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const XkvLayers& lay, int layers,
                      bool w_packed, uint16_t* cache, int H, int d, int frames_cap, hipStream_t st);
+// The same for a float32 model (row-major operands; e: the cache and its shape).
+void launch_xkv_f32(int M, int N, int K, const float* A, const XkvLayers& lay, int layers, const EpiArgs& e,
+                    hipStream_t st);
 // Row-major bf16 [M][K] (M a multiple of 16, K of 32) into the fragment order the
 // prefill reads (M * K elements).
 void launch_pack_rows(const uint16_t* A, int M, int K, uint16_t* P, hipStream_t st);

@@ -209,10 +209,10 @@ __global__ void __launch_bounds__(512) xkv_mfma_kernel(int M, int N, int K, cons
   const int m0 = (rem / gw) * X, n0 = (g * gc + rem % gw) * X;
   // a key tile (every column a key) swaps the product operands for its stores
   if (n0 + X <= d)
-    xkv_tile<T, true, APK, WPK>(M, N, K, A, lay.W[li], lay.bias[li], cache, lay.first + li, H, d, frames_cap, m0,
+    xkv_tile<T, true, APK, WPK>(M, N, K, A, (const uint16_t*)lay.W[li], (const uint16_t*)lay.bias[li], cache, lay.first + li, H, d, frames_cap, m0,
                                 n0, sa, sb);
   else
-    xkv_tile<T, false, APK, WPK>(M, N, K, A, lay.W[li], lay.bias[li], cache, lay.first + li, H, d, frames_cap,
+    xkv_tile<T, false, APK, WPK>(M, N, K, A, (const uint16_t*)lay.W[li], (const uint16_t*)lay.bias[li], cache, lay.first + li, H, d, frames_cap,
                                  m0, n0, sa, sb);
 }
 

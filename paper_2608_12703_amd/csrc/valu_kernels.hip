@@ -1,5 +1,5 @@
-// Vector-ALU matrix products and attention: the float32 model's path, and the
-// reference-shaped path every optimised kernel must agree with.
+// Float32 matrix products (on the float32 matrix instruction) and float32 attention (vector
+// ALU): the float32 model's path, and the products with float32 activations and bf16 weights.
 //
 // Every output element is reduced in a fixed order that does not depend on how many
 // rows share the launch, so a row's result is the same alone or inside any batch.
@@ -7,16 +7,6 @@
 #include "launch.h"
 
 namespace ad {
-
-// ---------------------------------------------------------------- GEMM
-// C[m][n] = sum_k A[m][k] W[n][k] (+ bias[n]); 32 x 64 output tile per 256 threads, K in
-// steps of 32 (K a multiple of 32).  Each output is one thread's fma chain over k in
-// order.  A step's operands pass through LDS; every thread requests its slice of the
-// operands kVStages steps ahead into registers, so a workgroup's K loop waits for memory
-// once rather than once per step (with few rows, as in batch-1 decoding, the loop is
-// otherwise a chain of dependent round trips).
-
-constexpr int kVStages = 8;
 
 // Workgroup barrier for LDS traffic only: this wave's LDS operations complete, its global
 // loads stay in flight (__syncthreads would also wait for every outstanding load, which
@@ -27,185 +17,217 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// One thread's slice of a K step: 4 activations of row ar; 8 weights (4 of rows wr and
-// wr + 32 in float32, or 8 of row wb in bf16).
-template <class S>
-struct VStage;
-template <>
-struct VStage<F32> {
-  float4 a, w0, w1;
-};
-template <>
-struct VStage<BF16> {
-  float4 a;
-  uint4 w;
-};
+// ---------------------------------------------------------------- GEMM
+// C[m][n] = sum_k A[m][k] W[n][k] (+ bias[n]), A float32, W float32 or bf16 (converted
+// exactly), K a multiple of 32, products and sums in float32 (v_mfma_f32_16x16x4_f32).
+//
+// A workgroup owns RT row tiles x CT column tiles of 16 x 16; its four waves take the four
+// quarters of K and their sums merge through LDS in quarter order.  What bounds these
+// products is latency (5 rows against 384 x 384 weights are 0.6 MB and 1.5 MFLOP), so K is
+// cut where the chain of dependent matrix instructions is, and the operands go straight
+// into registers D 32-wide steps ahead.  The quarters depend on K only.  A lane loads eight
+// consecutive k of its row, so an instruction's four k slots are k, k + 8, k + 16, k + 24 of
+// a step; both operands use the same slots.
+//
+// Against the vector-ALU product before it (32 x 64 tiles, one fma chain over K per output,
+// operands through LDS), 5 rows, us per launch: 384 x 384 and 384 x 1536 36.9 -> 5.5 on average,
+// QKV 22.2 -> 5.6, FFN-up 20.8 -> 4.6, the 51865-column LM head 35 -> 21 (3.8 TB/s); the four-layer
+// model's round at batch 1 1223 -> 508, its encoder K/V of 1500 frames 120 -> 70.  Each sum has
+// four shorter chains: the logits' error against 64 bits falls (1.2e-6 -> 0.7e-6).
 
-// Every load is issued unconditionally (rows and columns past the matrix read its last
-// row or column, steps past K its last step), so the number of loads in flight is the
-// same on every path and the compiler's waits count exactly; the values outside the
-// matrix become zeros when the step is staged in LDS.
+constexpr int kKQ = 4;   // K quarters, one wave each
+
 template <class S>
-__device__ __forceinline__ void vstage_load(VStage<S>& st, int kb, int M, int N, int K, const float* A,
-                                            const typename S::T* W, int m0, int n0, int tid) {
-  const int k0 = min(kb * 32, K - 32);
-  const int ar = tid >> 3, ak = (tid & 7) * 4;
-  st.a = *(const float4*)(A + (size_t)min(m0 + ar, M - 1) * K + k0 + ak);
-  if constexpr (sizeof(typename S::T) == 4) {
-    const int wr = tid >> 3, wk = (tid & 7) * 4;
-    st.w0 = *(const float4*)(W + (size_t)min(n0 + wr, N - 1) * K + k0 + wk);
-    st.w1 = *(const float4*)(W + (size_t)min(n0 + wr + 32, N - 1) * K + k0 + wk);
-  } else {
-    const int wb = tid >> 2, wk = (tid & 3) * 8;
-    st.w = *(const uint4*)(W + (size_t)min(n0 + wb, N - 1) * K + k0 + wk);
+struct FOperand;   // eight consecutive k of one row
+template <>
+struct FOperand<F32> {
+  float4 x, y;
+  __device__ __forceinline__ void load(const float* p) {
+    x = *(const float4*)p;
+    y = *(const float4*)(p + 4);
   }
-}
-
-// LDS layout of a step: activations transposed, At[k][row] (a row's 8 values of one k
-// are one broadcast read pair), weights Ws[col][k]; rows of 36 floats keep every
-// 16-byte read aligned and the weight reads of 16 lanes on distinct banks.
-constexpr int kVLd = 36;
-
-template <class S>
-__device__ __forceinline__ void vstage_put(const VStage<S>& st, int M, int N, int m0, int n0,
-                                           float (*At)[kVLd], float (*Ws)[kVLd], int tid) {
-  const int ar = tid >> 3, ak = (tid & 7) * 4;
-  const bool am = m0 + ar < M;
-  At[ak + 0][ar] = am ? st.a.x : 0.f;
-  At[ak + 1][ar] = am ? st.a.y : 0.f;
-  At[ak + 2][ar] = am ? st.a.z : 0.f;
-  At[ak + 3][ar] = am ? st.a.w : 0.f;
-  if constexpr (sizeof(typename S::T) == 4) {
-    const int wr = tid >> 3, wk = (tid & 7) * 4;
-    const bool w0 = n0 + wr < N, w1 = n0 + wr + 32 < N;
-    *(float4*)&Ws[wr][wk] = w0 ? st.w0 : float4{0.f, 0.f, 0.f, 0.f};
-    *(float4*)&Ws[wr + 32][wk] = w1 ? st.w1 : float4{0.f, 0.f, 0.f, 0.f};
-  } else {
-    const int wb = tid >> 2, wk = (tid & 3) * 8;
-    const bool wn = n0 + wb < N;
-    const uint32_t u[4] = {st.w.x, st.w.y, st.w.z, st.w.w};
-    float f[8];
+  __device__ __forceinline__ void get(float (&v)[8]) const {
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+  }
+};
+template <>
+struct FOperand<BF16> {
+  uint4 x;
+  __device__ __forceinline__ void load(const uint16_t* p) { x = *(const uint4*)p; }
+  __device__ __forceinline__ void get(float (&v)[8]) const {
+    const uint32_t u[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      f[2 * j] = wn ? bf16_to_f32(u[j] & 0xffff) : 0.f;
-      f[2 * j + 1] = wn ? bf16_to_f32(u[j] >> 16) : 0.f;
+      v[2 * j] = bf16_to_f32(u[j] & 0xffff);
+      v[2 * j + 1] = bf16_to_f32(u[j] >> 16);
     }
-    *(float4*)&Ws[wb][wk] = float4{f[0], f[1], f[2], f[3]};
-    *(float4*)&Ws[wb][wk + 4] = float4{f[4], f[5], f[6], f[7]};
   }
-}
+};
 
-template <class S, class SA, int EPI>
-__global__ void __launch_bounds__(256) gemm_valu_kernel(int M, int N, int K, const typename SA::T* A,
-                                                        const typename S::T* W,
-                                                        const typename S::T* bias, EpiArgs e) {
-  static_assert(sizeof(typename SA::T) == 4, "float32 activations");
-  __shared__ __align__(16) float At[32][kVLd];
-  __shared__ __align__(16) float Ws[64][kVLd];
-  const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 64;
-  const int KB = K / 32;
-  float acc[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) acc[r] = 0.f;
-  VStage<S> s0, s1, s2, s3, s4, s5, s6, s7;
-  vstage_load<S>(s0, 0, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s1, 1, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s2, 2, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s3, 3, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s4, 4, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s5, 5, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s6, 6, M, N, K, A, W, m0, n0, tid);
-  vstage_load<S>(s7, 7, M, N, K, A, W, m0, n0, tid);
-  // step kb: stage its operands in LDS, multiply, request step kb + kVStages into the
-  // freed registers
-#define VGEMM_STEP(ST, J)                                                 \
-  {                                                                       \
-    if (kb + (J) < KB) {                                                  \
-      lds_barrier();                                                      \
-      vstage_put<S>(ST, M, N, m0, n0, At, Ws, tid);                       \
-      lds_barrier();                                                      \
-      _Pragma("unroll") for (int k4 = 0; k4 < 32; k4 += 4) {              \
-        const float4 w = *(const float4*)&Ws[tx][k4];                     \
-        const float wv[4] = {w.x, w.y, w.z, w.w};                         \
-        _Pragma("unroll") for (int u = 0; u < 4; ++u) {                   \
-          const float4 a0 = *(const float4*)&At[k4 + u][ty * 8];          \
-          const float4 a1 = *(const float4*)&At[k4 + u][ty * 8 + 4];      \
-          const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}; \
-          _Pragma("unroll") for (int r = 0; r < 8; ++r) acc[r] = fmaf(av[r], wv[u], acc[r]); \
-        }                                                                 \
-      }                                                                   \
-    }                                                                     \
-    vstage_load<S>(ST, kb + (J) + kVStages, M, N, K, A, W, m0, n0, tid);  \
-  }
-  for (int kb = 0; kb < KB; kb += kVStages) {
-    VGEMM_STEP(s0, 0)
-    VGEMM_STEP(s1, 1)
-    VGEMM_STEP(s2, 2)
-    VGEMM_STEP(s3, 3)
-    VGEMM_STEP(s4, 4)
-    VGEMM_STEP(s5, 5)
-    VGEMM_STEP(s6, 6)
-    VGEMM_STEP(s7, 7)
-  }
-#undef VGEMM_STEP
-  const int n = n0 + tx;
-  if (n >= N) return;
-  const float bn = bias ? S::ld(bias, n) : 0.f;
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int m = m0 + ty * 8 + r;
-    if (m >= M) continue;
-    const float v = acc[r] + bn;
-    if (EPI == EPI_STORE) {
+// Where element (m, n) of the product goes.
+template <class S, int EPI>
+__device__ __forceinline__ void f32_epilogue(const EpiArgs& e, int m, int n, float v) {
+  if (EPI == EPI_STORE) {
+    e.out[(size_t)m * e.ldo + n] = v;
+  } else if (EPI == EPI_RESID) {
+    e.out[(size_t)m * e.ldo + n] += v;
+  } else if (EPI == EPI_GELU) {
+    e.out[(size_t)m * e.ldo + n] = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  } else if (EPI == EPI_QKV) {
+    if (n < e.d) {
       e.out[(size_t)m * e.ldo + n] = v;
-    } else if (EPI == EPI_RESID) {
-      e.out[(size_t)m * e.ldo + n] += v;
-    } else if (EPI == EPI_GELU) {
-      e.out[(size_t)m * e.ldo + n] = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-    } else if (EPI == EPI_QKV) {
-      if (n < e.d) {
-        e.out[(size_t)m * e.ldo + n] = v;
-      } else {
-        const RowDesc rd = e.rows[m];
-        if (rd.seq >= 0) {
-          const int c = n - e.d, kv = c / e.d, h = (c % e.d) / kHead, j = c % kHead;
-          int pg = e.block_table[(size_t)rd.seq * e.pages_per_seq + rd.slot / kTile];
-          pg = min(max(pg, 0), e.num_pages - 1);
-          S::st((typename S::T*)e.cache,
-                kv_tile_base(e.layer, kv, pg, h, e.num_pages, e.H) + tile_off(kv, rd.slot % kTile, j), v);
-        }
+    } else {
+      const RowDesc rd = e.rows[m];
+      if (rd.seq >= 0) {
+        const int c = n - e.d, kv = c / e.d, h = (c % e.d) / kHead, j = c % kHead;
+        int pg = e.block_table[(size_t)rd.seq * e.pages_per_seq + rd.slot / kTile];
+        pg = min(max(pg, 0), e.num_pages - 1);
+        S::st((typename S::T*)e.cache,
+              kv_tile_base(e.layer, kv, pg, h, e.num_pages, e.H) + tile_off(kv, rd.slot % kTile, j), v);
       }
-    } else if (EPI == EPI_XKV) {
-      const int kv = n / e.d, h = (n % e.d) / kHead, j = n % kHead;
-      S::st((typename S::T*)e.cache, cross_base(e.layer, h, e.H, e.frames_cap) + cross_off(kv, m, j), v);
+    }
+  } else if (EPI == EPI_XKV) {
+    const int kv = n / e.d, h = (n % e.d) / kHead, j = n % kHead;
+    S::st((typename S::T*)e.cache, cross_base(e.layer, h, e.H, e.frames_cap) + cross_off(kv, m, j), v);
+  }
+}
+
+template <class S, int EPI, int RT, int CT, int D>
+__device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* A, const typename S::T* W,
+                                              const typename S::T* bias, const EpiArgs& e, int m0, int n0,
+                                              f32x4 (*part)[RT * CT][kWave]) {
+  const int lane = threadIdx.x & 63, c16 = lane & 15, grp = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KB = K / 32, kb0 = (w * KB) / kKQ, kb1 = ((w + 1) * KB) / kKQ, kl = max(kb1 - 1, kb0);
+  // rows and columns past the matrix read its last (those results are never stored)
+  const float* pa[RT];
+  const typename S::T* pw[CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) pa[r] = A + (size_t)min(m0 + r * 16 + c16, M - 1) * K + grp * 8;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) pw[c] = W + (size_t)min(n0 + c * 16 + c16, N - 1) * K + grp * 8;
+  struct Stage {
+    FOperand<F32> a[RT];
+    FOperand<S> w[CT];
+  };
+  auto load = [&](Stage& st, int kb) __attribute__((always_inline)) {
+    const int k = min(min(kb, kl), KB - 1) * 32;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) st.w[c].load(pw[c] + k);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) st.a[r].load(pa[r] + k);
+  };
+  f32x4 acc[RT][CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](const Stage& st) __attribute__((always_inline)) {
+    float av[RT][8], wv[CT][8];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) st.a[r].get(av[r]);
+#pragma unroll
+    for (int c = 0; c < CT; ++c) st.w[c].get(wv[c]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r][j], wv[c][j], acc[r][c], 0, 0, 0);
+  };
+  Stage st[D];
+#pragma unroll
+  for (int u = 0; u < D; ++u) load(st[u], kb0 + u);
+  int kb = kb0;
+  for (int it = 0; it < (kb1 - kb0 - 1) / D; ++it) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      mma(st[u]);
+      load(st[u], kb + D + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    kb += D;
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (kb + u < kb1) mma(st[u]);
+
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) part[w][r * CT + c][lane] = acc[r][c];
+  lds_barrier();
+  // the quarters in order; wave w finishes tiles w, w + 4, ...
+  for (int t = w; t < RT * CT; t += kKQ) {
+    f32x4 v = part[0][t][lane];
+#pragma unroll
+    for (int q = 1; q < kKQ; ++q) v += part[q][t][lane];
+    const int n = n0 + (t % CT) * 16 + c16;
+    if (n >= N) continue;
+    const float bn = bias ? S::ld(bias, n) : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = m0 + (t / CT) * 16 + grp * 4 + i;
+      if (m < M) f32_epilogue<S, EPI>(e, m, n, v[i] + bn);
     }
   }
 }
 
-template <class S, class SA>
-static void gemm_valu_dispatch(int epi, int M, int N, int K, const void* A, const void* W,
-                               const void* bias, const EpiArgs& e, hipStream_t st) {
-  const dim3 grid((N + 63) / 64, (M + 31) / 32), block(256);
-  const auto* a = (const typename SA::T*)A;
+template <class S, int EPI, int RT, int CT, int D>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(int M, int N, int K, const float* A,
+                                                       const typename S::T* W, const typename S::T* bias,
+                                                       EpiArgs e) {
+  __shared__ f32x4 part[kKQ][RT * CT][kWave];
+  gemm_f32_tile<S, EPI, RT, CT, D>(M, N, K, A, W, bias, e, blockIdx.y * RT * 16, blockIdx.x * CT * 16, part);
+}
+
+// The encoder K/V of several layers (blockIdx.z).
+__global__ void __launch_bounds__(256) xkv_f32_kernel(int M, int N, int K, const float* A, XkvLayers lay,
+                                                      EpiArgs e) {
+  __shared__ f32x4 part[kKQ][16][kWave];
+  const int li = blockIdx.z;
+  e.layer = lay.first + li;
+  gemm_f32_tile<F32, EPI_XKV, 4, 4, 2>(M, N, K, A, (const float*)lay.W[li], (const float*)lay.bias[li], e,
+                                       blockIdx.y * 64, blockIdx.x * 64, part);
+}
+
+// Tile: one 16 x 16 tile per workgroup while that fills the chip less than eight times over
+// (the most waves for the least latency), else four column tiles and as many row tiles as
+// there are, up to four (operand bytes per product fall with the tile).
+template <class S, int EPI>
+static void launch_f32(int M, int N, int K, const float* A, const void* W, const void* bias, const EpiArgs& e,
+                       hipStream_t st) {
   const auto* w = (const typename S::T*)W;
   const auto* b = (const typename S::T*)bias;
-  switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm_valu_kernel<S, SA, EPI_STORE>), grid, block, 0, st, M, N, K, a, w, b, e); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_valu_kernel<S, SA, EPI_RESID>), grid, block, 0, st, M, N, K, a, w, b, e); break;
-    case EPI_GELU: hipLaunchKernelGGL((gemm_valu_kernel<S, SA, EPI_GELU>), grid, block, 0, st, M, N, K, a, w, b, e); break;
-    case EPI_QKV: hipLaunchKernelGGL((gemm_valu_kernel<S, SA, EPI_QKV>), grid, block, 0, st, M, N, K, a, w, b, e); break;
-    case EPI_XKV: hipLaunchKernelGGL((gemm_valu_kernel<S, SA, EPI_XKV>), grid, block, 0, st, M, N, K, a, w, b, e); break;
-  }
+  const int MT = (M + 15) / 16, NT = (N + 15) / 16;
+  auto go = [&](auto kernel, int rt, int ct) {
+    hipLaunchKernelGGL(kernel, dim3((NT + ct - 1) / ct, (MT + rt - 1) / rt), dim3(256), 0, st, M, N, K, A, w, b, e);
+  };
+  if ((long long)MT * NT <= 2048) go(gemm_f32_kernel<S, EPI, 1, 1, 4>, 1, 1);
+  else if (MT == 1) go(gemm_f32_kernel<S, EPI, 1, 4, 3>, 1, 4);
+  else if (MT == 2) go(gemm_f32_kernel<S, EPI, 2, 4, 3>, 2, 4);
+  else go(gemm_f32_kernel<S, EPI, 4, 4, 2>, 4, 4);
 }
 
 template <class S>
-void launch_gemm_valu(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
-                      const EpiArgs& e, hipStream_t st) {
-  gemm_valu_dispatch<S, F32>(epi, M, N, K, A, W, bias, e, st);
+void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
+                     const EpiArgs& e, hipStream_t st) {
+  if (epi == EPI_STORE) launch_f32<S, EPI_STORE>(M, N, K, A, W, bias, e, st);
+  if constexpr (sizeof(typename S::T) == 4) {
+    if (epi == EPI_RESID) launch_f32<S, EPI_RESID>(M, N, K, A, W, bias, e, st);
+    else if (epi == EPI_GELU) launch_f32<S, EPI_GELU>(M, N, K, A, W, bias, e, st);
+    else if (epi == EPI_QKV) launch_f32<S, EPI_QKV>(M, N, K, A, W, bias, e, st);
+  }
 }
-template void launch_gemm_valu<F32>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
-template void launch_gemm_valu<BF16>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_gemm_f32<BF16>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+
+void launch_xkv_f32(int M, int N, int K, const float* A, const XkvLayers& lay, int layers, const EpiArgs& e,
+                    hipStream_t st) {
+  hipLaunchKernelGGL(xkv_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64, layers), dim3(256), 0, st, M, N, K, A, lay, e);
+}
 
 // ---------------------------------------------------------------- attention
 // One block per (head, sequence, group of kVGroupKeys keys at absolute positions 0, 128,

@@ -4,7 +4,8 @@ A launch with few 16 x 16 output tiles runs the register-direct product (one to 
 per wave), a larger one the LDS product, and the LM head switches at 1, 2, 3, 5-6 row tiles.
 One row per sequence: the same sequences in batches of every size must give the same bits
 (the order of a row's sums never depends on the launch), and the rows must match the oracle.
-Widths: 192 (not a multiple of the 128-column weight tile, odd vocabulary) and 1280 (the
+The float32 product changes its tile by the number of 16 x 16 output tiles (the vocabulary of
+33001 columns reaches its larger ones at every row count).  Widths: 192 (not a multiple of the 128-column weight tile, odd vocabulary) and 1280 (the
 two-row-tile waves).  Tolerance against the oracle: the logit bar of the parity tests.
 """
 import numpy as np
@@ -12,7 +13,7 @@ import pytest
 import torch
 
 from oracle import decoder as od
-from paper_2608_12703_amd import synth
+from paper_2608_12703_amd import ad, synth
 from paper_2608_12703_amd.configs import Config
 from paper_2608_12703_amd.harness import Session, upload_params
 
@@ -32,14 +33,16 @@ def _run(cfg, plist, encs, tokens, pack):
     return r
 
 
-@pytest.mark.parametrize("d,ffn,vocab,rows,pack", [
-    (192, 384, 1003, (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 81, 96, 97, 112), True),
-    (192, 384, 1003, (1, 33, 81), False),
-    (1280, 5120, 517, (16, 17, 49, 80, 81, 112), True),
+@pytest.mark.parametrize("dtype,d,ffn,vocab,rows,pack", [
+    ("bf16", 192, 384, 1003, (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 81, 96, 97, 112), True),
+    ("bf16", 192, 384, 1003, (1, 33, 81), False),
+    ("bf16", 1280, 5120, 517, (16, 17, 49, 80, 81, 112), True),
+    ("f32", 192, 384, 33001, (1, 16, 17, 32, 33, 49), False),
+    ("f32", 64, 64, 1003, (1, 17, 33), False),
 ])
-def test_rows_do_not_depend_on_the_launch(d, ffn, vocab, rows, pack):
-    top = 200    # 13 row tiles
-    cfg = Config(name="rows", n_layers=1, d_model=d, n_heads=d // 64, d_ffn=ffn, vocab=vocab, dtype="bf16",
+def test_rows_do_not_depend_on_the_launch(dtype, d, ffn, vocab, rows, pack):
+    top = 200 if dtype == "bf16" else 70    # 13 and 5 row tiles
+    cfg = Config(name="rows", n_layers=1, d_model=d, n_heads=d // 64, d_ffn=ffn, vocab=vocab, dtype=dtype,
                  batch=top, k=0, frames=FRAMES, seed=21)
     params = synth.make_params(cfg)
     plist = upload_params(cfg, params)
@@ -47,9 +50,9 @@ def test_rows_do_not_depend_on_the_launch(d, ffn, vocab, rows, pack):
     tokens = [int(t) for t in np.random.default_rng(4).integers(0, vocab, top)]
     full = _run(cfg, plist, encs, tokens, pack)
     model = od.Model(cfg, params)
-    for b in (0, 16, 111):
+    for b in (0, 16, top - 1):
         ref = od.verify(model, od.new_state(model, od.cross_kv(model, encs[b]), tokens[b]), np.zeros(0, np.int64))
-        assert float(np.max(np.abs(full["logits"][b] - ref.logits[0]))) <= LOGIT_TOL["bf16"]
+        assert float(np.max(np.abs(full["logits"][b] - ref.logits[0]))) <= LOGIT_TOL[dtype]
     for n in rows:
         got = _run(cfg, plist, encs, tokens[:n], pack)
         for key in ("hidden", "logits", "margin"):
@@ -57,3 +60,27 @@ def test_rows_do_not_depend_on_the_launch(d, ffn, vocab, rows, pack):
                                           err_msg=f"{key} at {n} rows")
         np.testing.assert_array_equal(got["greedy"], full["greedy"][:n])
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("batch,n_heads", [(1, 4), (17, 2), (33, 1)])
+def test_bf16_draft_heads_pick_the_largest_logit(batch, n_heads):
+    """Drafts of bf16 heads against the float64 products (a draft may differ only where the
+    float64 logits tie within 1e-5, far above the float32 sums' error of ~1e-6)."""
+    d, vocab, k = 192, 5003, 2
+    cfg = Config(name="heads", n_layers=1, d_model=d, n_heads=3, d_ffn=64, vocab=vocab, dtype="bf16", batch=batch,
+                 k=k, frames=32, seed=8)
+    s = Session(cfg, synth.make_params(cfg), batch, k, [32] * batch)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    w = (torch.randn(n_heads, vocab, d, generator=g, device="cuda") * 0.02).bfloat16()
+    hidden = torch.randn(batch * (k + 1), d, generator=g, device="cuda")
+    r = np.random.default_rng(2)
+    acc = torch.tensor(r.integers(0, k + 1, batch), dtype=torch.int32, device="cuda")
+    toks = torch.tensor(r.integers(0, vocab, (batch, k + 1)), dtype=torch.int32, device="cuda")
+    nxt = torch.zeros(batch, n_heads + 1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(s.model.draft_heads_workspace_size(n_heads, batch), dtype=torch.uint8, device="cuda")
+    ad.draft_heads(s.model, w, n_heads, hidden, ad.AD_PADDED, k, None, acc, toks, batch, nxt, ws)
+    row = torch.arange(batch, device="cuda") * (k + 1) + acc
+    for i in range(n_heads):
+        z = hidden[row].double() @ w[i].double().T
+        assert torch.all(z.gather(1, nxt[:, 1 + i: 2 + i].long())[:, 0] >= z.max(-1).values - 1e-5)
+    assert torch.equal(nxt[:, 0], toks[torch.arange(batch), acc.long()])
