@@ -87,12 +87,11 @@ struct Workspace {
   float* apart;    // float32 path: attention partials per key group
   int gself, gcross;   // float32 path: key groups of self- and cross-attention
   float* hidden;   // final LayerNorm output [M][d]
-  float* logits;   // float32 path: [M][V]
   int* greedy;     // [M]
   uint16_t* afrag; // bf16 path: d-wide product operand, A-fragment order
   uint16_t* hfrag; // bf16 path: F-wide product operand (GELU output)
   float* gpart;    // bf16 path: split-K partial products
-  void* ampart;    // bf16 path: LM-head top-2 records
+  void* ampart;    // LM-head top-2 records
   float* q_anchor; // the anchor layer's cross-attention queries [M][d]
   float* xscore;   // anchor readout scratch (scores, then per-chunk statistics)
   unsigned long long* abest;   // fused readout: per-sequence merged best
@@ -130,7 +129,7 @@ Workspace carve(const ad_model_desc& d, int M, int B, int k_max, char* base) {
     w.gself = ad::attn_valu_groups(d.max_pos);
     w.gcross = ad::attn_valu_groups(d.max_frames);
     w.apart = (float*)take(4 * ad::attn_valu_part_floats(M, d.n_heads, std::max(w.gself, w.gcross)));
-    w.logits = (float*)take(4 * M * V);
+    w.ampart = take(16ull * M * ad::f32_records((int)V));
   } else {
     const int Mp = w.RT * 16;
     w.afrag = (uint16_t*)take(4ull * Mp * D);
@@ -282,14 +281,12 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
   }
   float* hidden = s->out_hidden ? s->out_hidden : w.hidden;
   ad::launch_layernorm<S>(M, d, w.x, m->p[P_LNF_G], m->p[P_LNF_B], hidden, st);
-  float* logits = s->out_logits ? s->out_logits : w.logits;
-  e.out = logits; e.ldo = V;
   {
     ProfScope ps(m, AD_PROF_LM_HEAD, st);
-    ad::launch_gemm_f32<S>(ad::EPI_STORE, M, V, d, hidden, m->p[P_TOK], nullptr, e, st);
+    ad::launch_f32_head_argmax<S>(1, M, V, d, hidden, m->p[P_TOK], w.ampart, s->out_logits, st);
   }
   int* greedy = s->out_greedy ? s->out_greedy : w.greedy;
-  ad::launch_argmax(M, V, logits, V, w.rows, greedy, s->out_margin, s->err_flag, st);
+  ad::launch_argmax_final(M, ad::f32_records(V), w.ampart, w.rows, greedy, s->out_margin, s->err_flag, st);
   accept(s, w, greedy, st);
   if (s->anchor_layer >= 0) ad::launch_anchor<S>(anchor_args(m, s, w), s->batch, st);
 }
@@ -739,19 +736,16 @@ ad_status ad_draft_input(const ad_model* model, const void* w_fuse, const void* 
   const float* f = feature;
   ad::EpiArgs e{};
   e.ldo = d;
-  const bool bf16 = false;
   if (taps) {
     ad::launch_draft_gather_taps(batch, d, layout, k_max, cu_rows, accept_len, rows, taps, hidden,
                                  taps4, st);
     e.out = feat;
-    if (bf16) ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
-    else ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
+    ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
     f = feat;
   }
-  ad::launch_draft_concat(batch, d, f, model->p[P_TOK], bf16, tokens, token_stride, token_index, z, st);
+  ad::launch_draft_concat(batch, d, f, model->p[P_TOK], tokens, token_stride, token_index, z, st);
   e.out = out;
-  if (bf16) ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
-  else ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
+  ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
   if (anchor) ad::launch_draft_window(batch, anchor, enc_len, half_window, window, st);
   return check_hip("ad_draft_input");
 }
@@ -926,7 +920,7 @@ ad_status ad_draft_heads_workspace_size(const ad_model* model, int32_t n_heads, 
   if (!model || !bytes) return fail(AD_EINVAL, "NULL argument");
   if (n_heads < 1 || batch < 1) return fail(AD_ERANGE, "n_heads and batch must be positive");
   const ad_model_desc& D = model->desc;
-  *bytes = align256(4ull * batch * D.d_model) + align256(4ull * n_heads * batch * D.vocab) +
+  *bytes = align256(4ull * batch * D.d_model) + align256(16ull * n_heads * batch * ad::f32_records(D.vocab)) +
            align256(4ull * n_heads * batch);
   return AD_OK;
 }
@@ -948,25 +942,18 @@ ad_status ad_draft_heads(const ad_model* model, const void* heads_w, int32_t n_h
   char* base = (char*)workspace;
   float* hsel = (float*)base;
   base += align256(4ull * batch * D.d_model);
-  float* logits = (float*)base;
-  base += align256(4ull * n_heads * batch * D.vocab);
+  void* records = base;
+  base += align256(16ull * n_heads * batch * ad::f32_records(D.vocab));
   int* greedy = (int*)base;
   (void)hipGetLastError();
   hipStream_t st = (hipStream_t)stream;
   ad::launch_gather_hidden(batch, D.d_model, layout, k_max, cu_rows, accept_len, hidden, hsel, st);
-  const size_t esz = D.dtype == AD_BF16 ? 2 : 4;
-  ad::EpiArgs e{};
-  for (int i = 0; i < n_heads; ++i) {
-    e.out = logits + (size_t)i * batch * D.vocab;
-    e.ldo = D.vocab;
-    const void* w = (const char*)heads_w + (size_t)i * D.vocab * D.d_model * esz;
-    if (D.dtype == AD_BF16)
-      ad::launch_gemm_f32<ad::BF16>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
-    else
-      ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, D.vocab, D.d_model, hsel, w, nullptr, e, st);
-  }
+  if (D.dtype == AD_BF16)
+    ad::launch_f32_head_argmax<ad::BF16>(n_heads, batch, D.vocab, D.d_model, hsel, heads_w, records, nullptr, st);
+  else
+    ad::launch_f32_head_argmax<ad::F32>(n_heads, batch, D.vocab, D.d_model, hsel, heads_w, records, nullptr, st);
   // the err flag of the step is not touched here: non-finite head logits give -1 drafts
-  ad::launch_argmax(n_heads * batch, D.vocab, logits, D.vocab, nullptr, greedy, nullptr, nullptr, st);
+  ad::launch_argmax_final(n_heads * batch, ad::f32_records(D.vocab), records, nullptr, greedy, nullptr, nullptr, st);
   ad::launch_assemble_next(batch, n_heads, k_max, accept_len, out_tokens, greedy, next_tokens, st);
   return check_hip("ad_draft_heads");
 }

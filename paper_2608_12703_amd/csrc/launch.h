@@ -59,8 +59,6 @@ void launch_embed(int M, int d, const RowDesc* rows, const void* tok, const void
 template <class S>
 void launch_layernorm(int M, int d, const float* x, const void* g, const void* b, float* out,
                       hipStream_t st);
-void launch_argmax(int M, int V, const float* logits, size_t ld, const RowDesc* rows, int* greedy,
-                   float* margin, int* err, hipStream_t st);
 void launch_accept(int B, int k_max, const SeqDesc* seqs, const int* tokens, const int* greedy,
                    int* accept_len, int* out_tokens, hipStream_t st);
 void launch_commit(int B, int* kv_len, const int* accept_len, hipStream_t st);
@@ -85,6 +83,13 @@ void launch_assemble_next(int B, int n_heads, int k_max, const int* accept_len, 
 
 // C = A W^T (+ bias) in float32 with the epilogue `epi` (EPI_STORE, and for float32 weights
 // EPI_RESID, EPI_GELU, EPI_QKV); A is float32 [M][K], W is [N][K] of S.
+// f32_head_argmax: `heads` products with the same A, W [heads][N][K]: per row and 64 columns a
+// top-2 record, float4 am_part[heads][M][f32_records(N)] (merged by launch_argmax_final), and
+// the logits [heads][M][N] when `logits` is given.
+int f32_records(int N);
+template <class S>
+void launch_f32_head_argmax(int heads, int M, int N, int K, const float* A, const void* W, void* am_part,
+                            float* logits, hipStream_t st);
 template <class S>
 void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
                       const EpiArgs& e, hipStream_t st);
@@ -256,7 +261,7 @@ void launch_embed_ln(int M, int d, const RowDesc* rows, const void* tok, const v
 void launch_draft_gather_taps(int B, int d, int layout, int k_max, const int* cu_rows,
                               const int* accept_len, int rows, const float* taps,
                               const float* hidden, float* taps4, hipStream_t st);
-void launch_draft_concat(int B, int d, const float* feat, const void* tok_emb, int bf16,
+void launch_draft_concat(int B, int d, const float* feat, const void* tok_emb,
                          const int* tokens, int token_stride, const int* token_index, float* z,
                          hipStream_t st);
 void launch_draft_window(int B, const int* anchor, const int* enc_len, int half, int* window,

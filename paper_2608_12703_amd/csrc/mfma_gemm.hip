@@ -33,56 +33,6 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
 }
 
-// Running top-2 of a set of logits: largest value v1 at index i1 (lowest index among
-// equal maxima), the runner-up value v2 (equal to v1 when the maximum repeats), and
-// whether a non-finite value was seen.  The merge is associative and commutative, so any
-// reduction order gives the same record.  Branch-free (selects only).
-struct Top2s {
-  float v1;
-  int i1;
-  float v2;
-  int bad;
-};
-__device__ __forceinline__ Top2s t2_merge(Top2s a, Top2s b) {
-  const bool aw = (a.v1 > b.v1) | ((a.v1 == b.v1) & (a.i1 < b.i1));
-  Top2s r;
-  r.v1 = aw ? a.v1 : b.v1;
-  r.i1 = aw ? a.i1 : b.i1;
-  r.v2 = fmaxf(aw ? a.v2 : b.v2, aw ? b.v1 : a.v1);
-  r.bad = a.bad | b.bad;
-  return r;
-}
-__device__ __forceinline__ Top2s t2_shfl(Top2s t, int mask) {
-  Top2s u;
-  u.v1 = __shfl_xor(t.v1, mask, kWave);
-  u.i1 = __shfl_xor(t.i1, mask, kWave);
-  u.v2 = __shfl_xor(t.v2, mask, kWave);
-  u.bad = __shfl_xor(t.bad, mask, kWave);
-  return u;
-}
-// Rotate by N lanes inside each row of 16 lanes (DPP row_ror, no LDS round trip).
-template <int N>
-__device__ __forceinline__ int ror16(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false);
-}
-template <int N>
-__device__ __forceinline__ Top2s t2_ror16(Top2s t) {
-  Top2s u;
-  u.v1 = __int_as_float(ror16<N>(__float_as_int(t.v1)));
-  u.i1 = ror16<N>(t.i1);
-  u.v2 = __int_as_float(ror16<N>(__float_as_int(t.v2)));
-  u.bad = ror16<N>(t.bad);
-  return u;
-}
-// Merge over the 16 lanes of a row: afterwards every lane holds the row's record.
-__device__ __forceinline__ Top2s t2_row16(Top2s t) {
-  t = t2_merge(t, t2_ror16<8>(t));
-  t = t2_merge(t, t2_ror16<4>(t));
-  t = t2_merge(t, t2_ror16<2>(t));
-  t = t2_merge(t, t2_ror16<1>(t));
-  return t;
-}
-
 // Wait until at most N vector-memory operations of this wave are outstanding (they
 // complete in order) and its LDS operations are done, then barrier.  No memory fence.
 // The gfx9 s_waitcnt immediate holds vmcnt in two fields: bits 3:0 and bits 15:14
@@ -741,27 +691,6 @@ __global__ void __launch_bounds__(256) pack_weight_kernel(const uint16_t* W, int
   }
 }
 
-// Row-wise merge of the per-tile top-2 records of the LM head: greedy token (lowest
-// index among equal maxima) and the top-1 minus top-2 margin.
-__global__ void __launch_bounds__(64) argmax_final_kernel(int M, int nrec, const float4* part,
-                                                          const RowDesc* rows, int* greedy,
-                                                          float* margin, int* err) {
-  const int m = blockIdx.x, lane = threadIdx.x;
-  Top2s t{-INFINITY, 0x7fffffff, -INFINITY, 0};
-  for (int j = lane; j < nrec; j += 64) {
-    const float4 p = part[(size_t)m * nrec + j];
-    t = t2_merge(t, Top2s{p.x, __float_as_int(p.y), p.z, __float_as_int(p.w)});
-  }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) t = t2_merge(t, t2_shfl(t, o));
-  if (lane == 0) {
-    const bool valid_row = rows ? rows[m].seq >= 0 : true;
-    if (t.bad && valid_row && err) atomicOr(err, 16);
-    greedy[m] = (t.bad && valid_row) ? -1 : t.i1;
-    if (margin) margin[m] = t.v1 - t.v2;
-  }
-}
-
 // Launch planning.  A workgroup's time is dominated by fixed costs (first-load latency,
 // the partial stores) plus its K steps, and a second round of workgroups costs a whole
 // extra pass, so plans keep the grid within one workgroup per CU.  Per-step times for
@@ -935,13 +864,6 @@ void launch_gemm_mfma(int epi, GemmArgs g, hipStream_t st) {
   if (epi == EPI_ARGMAX) launch_one<EPI_ARGMAX>(g, st);
   else if (epi == EPI_GELU) launch_one<EPI_GELU>(g, st);
   else launch_one<EPI_PARTIAL>(g, st);
-}
-
-
-void launch_argmax_final(int M, int nrec, const void* part, const RowDesc* rows, int* greedy,
-                         float* margin, int* err, hipStream_t st) {
-  hipLaunchKernelGGL(argmax_final_kernel, dim3(M), dim3(64), 0, st, M, nrec, (const float4*)part,
-                     rows, greedy, margin, err);
 }
 
 }  // namespace ad

@@ -303,67 +303,25 @@ __global__ void zero_i32_kernel(int* p, int n) {
 }
 
 // ---------------------------------------------------------------- argmax + margin
-// Per row: largest logit (lowest index on ties) and the runner-up value.
 
-struct Top2 {
-  float v1;
-  int i1;
-  float v2;
-};
-__device__ __forceinline__ Top2 top2_merge(Top2 a, Top2 b) {
-  const bool a_wins = (a.v1 > b.v1) || (a.v1 == b.v1 && a.i1 < b.i1);
-  Top2 r;
-  if (a_wins) { r.v1 = a.v1; r.i1 = a.i1; r.v2 = fmaxf(a.v2, b.v1); }
-  else        { r.v1 = b.v1; r.i1 = b.i1; r.v2 = fmaxf(b.v2, a.v1); }
-  return r;
-}
-
-__global__ void __launch_bounds__(256) argmax_kernel(int V, const float* logits, size_t ld,
-                                                     const RowDesc* rows, int* greedy,
-                                                     float* margin, int* err) {
-  __shared__ Top2 red[4];
-  __shared__ int bad_s;
-  const int m = blockIdx.x;
-  const float* lr = logits + (size_t)m * ld;
-  if (threadIdx.x == 0) bad_s = 0;
-  __syncthreads();
-  Top2 t{-INFINITY, 0x7fffffff, -INFINITY};
-  int bad = 0;
-  // this thread's indices j = tid, tid + 256, ... in increasing order; sixteen loads are
-  // requested before they are used (a row's scan is otherwise one round trip per value)
-  auto take = [&](float v, int j) {
-    if (!isfinite(v)) { bad = 1; return; }
-    if (v > t.v1) { t.v2 = t.v1; t.v1 = v; t.i1 = j; }
-    else if (v > t.v2) { t.v2 = v; }
-  };
-  int j0 = threadIdx.x;
-  for (; j0 + 15 * 256 < V; j0 += 16 * 256) {
-    float v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = lr[j0 + u * 256];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) take(v[u], j0 + u * 256);
+// Row-wise merge of the per-tile top-2 records of the LM head: greedy token (lowest
+// index among equal maxima) and the top-1 minus top-2 margin.
+__global__ void __launch_bounds__(64) argmax_final_kernel(int M, int nrec, const float4* part,
+                                                          const RowDesc* rows, int* greedy,
+                                                          float* margin, int* err) {
+  const int m = blockIdx.x, lane = threadIdx.x;
+  Top2s t{-INFINITY, 0x7fffffff, -INFINITY, 0};
+  for (int j = lane; j < nrec; j += 64) {
+    const float4 p = part[(size_t)m * nrec + j];
+    t = t2_merge(t, Top2s{p.x, __float_as_int(p.y), p.z, __float_as_int(p.w)});
   }
-  for (int j = j0; j < V; j += 256) take(lr[j], j);
-  if (bad) atomicOr(&bad_s, 1);
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    Top2 u;
-    u.v1 = __shfl_xor(t.v1, o, kWave);
-    u.i1 = __shfl_xor(t.i1, o, kWave);
-    u.v2 = __shfl_xor(t.v2, o, kWave);
-    t = top2_merge(t, u);
-  }
-  const int w = threadIdx.x / kWave;
-  if (threadIdx.x % kWave == 0) red[w] = t;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    Top2 r = red[0];
-    for (int i = 1; i < 4; ++i) r = top2_merge(r, red[i]);
+  for (int o = 1; o < 64; o <<= 1) t = t2_merge(t, t2_shfl(t, o));
+  if (lane == 0) {
     const bool valid_row = rows ? rows[m].seq >= 0 : true;
-    if (bad_s && valid_row && err) atomicOr(err, 16);
-    greedy[m] = (bad_s && valid_row) ? -1 : r.i1;
-    if (margin) margin[m] = r.v1 - r.v2;
+    if (t.bad && valid_row && err) atomicOr(err, 16);
+    greedy[m] = (t.bad && valid_row) ? -1 : t.i1;
+    if (margin) margin[m] = t.v1 - t.v2;
   }
 }
 
@@ -766,15 +724,11 @@ void launch_draft_gather_taps(int B, int d, int layout, int k_max, const int* cu
                      accept_len, rows, taps, hidden, taps4);
 }
 
-void launch_draft_concat(int B, int d, const float* feat, const void* tok_emb, int bf16,
-                         const int* tokens, int token_stride, const int* token_index, float* z,
+void launch_draft_concat(int B, int d, const float* feat, const void* tok_emb, const int* tokens,
+                         int token_stride, const int* token_index, float* z,
                          hipStream_t st) {
-  if (bf16)
-    hipLaunchKernelGGL(draft_concat_kernel<BF16>, dim3(B), dim3(256), 0, st, d, feat,
-                       (const uint16_t*)tok_emb, tokens, token_stride, token_index, z);
-  else
-    hipLaunchKernelGGL(draft_concat_kernel<F32>, dim3(B), dim3(256), 0, st, d, feat,
-                       (const float*)tok_emb, tokens, token_stride, token_index, z);
+  hipLaunchKernelGGL(draft_concat_kernel<F32>, dim3(B), dim3(256), 0, st, d, feat, (const float*)tok_emb, tokens,
+                     token_stride, token_index, z);
 }
 
 void launch_draft_window(int B, const int* anchor, const int* enc_len, int half, int* window,
@@ -788,9 +742,10 @@ void launch_zero_i32(int* p, int n, hipStream_t st) {
   hipLaunchKernelGGL(zero_i32_kernel, dim3(min((n + 255) / 256, 1024)), dim3(256), 0, st, p, n);
 }
 
-void launch_argmax(int M, int V, const float* logits, size_t ld, const RowDesc* rows, int* greedy,
-                   float* margin, int* err, hipStream_t st) {
-  hipLaunchKernelGGL(argmax_kernel, dim3(M), dim3(256), 0, st, V, logits, ld, rows, greedy, margin, err);
+void launch_argmax_final(int M, int nrec, const void* part, const RowDesc* rows, int* greedy,
+                         float* margin, int* err, hipStream_t st) {
+  hipLaunchKernelGGL(argmax_final_kernel, dim3(M), dim3(64), 0, st, M, nrec, (const float4*)part,
+                     rows, greedy, margin, err);
 }
 
 void launch_accept(int B, int k_max, const SeqDesc* seqs, const int* tokens, const int* greedy,

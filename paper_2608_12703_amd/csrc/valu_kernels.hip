@@ -25,9 +25,7 @@ __device__ __forceinline__ void lds_barrier() {
 // quarters of K and their sums merge through LDS in quarter order.  What bounds these
 // products is latency (5 rows against 384 x 384 weights are 0.6 MB and 1.5 MFLOP), so K is
 // cut where the chain of dependent matrix instructions is, and the operands go straight
-// into registers D 32-wide steps ahead.  The quarters depend on K only.  A lane loads eight
-// consecutive k of its row, so an instruction's four k slots are k, k + 8, k + 16, k + 24 of
-// a step; both operands use the same slots.
+// into registers D 32-wide steps ahead.  The quarters depend on K only.
 //
 // Against the vector-ALU product before it (32 x 64 tiles, one fma chain over K per output,
 // operands through LDS), 5 rows, us per launch: 384 x 384 and 384 x 1536 36.9 -> 5.5 on average,
@@ -37,14 +35,19 @@ __device__ __forceinline__ void lds_barrier() {
 
 constexpr int kKQ = 4;   // K quarters, one wave each
 
-template <class S>
-struct FOperand;   // eight consecutive k of one row
-template <>
-struct FOperand<F32> {
+// Eight k of one row of a 32-wide step for lane group grp: with float32 weights k = 4 grp + j
+// and 16 + 4 grp + j (each load takes 64 consecutive bytes of 16 rows), with bf16 weights
+// k = 8 grp + j.  Both operands of a product use the same.
+template <class S, class W>
+struct FOperand;
+template <class W>
+struct FOperand<F32, W> {
+  static constexpr bool kWide = sizeof(typename W::T) == 4;
   float4 x, y;
+  static __device__ __forceinline__ int first(int grp) { return kWide ? grp * 4 : grp * 8; }
   __device__ __forceinline__ void load(const float* p) {
     x = *(const float4*)p;
-    y = *(const float4*)(p + 4);
+    y = *(const float4*)(p + (kWide ? 16 : 4));
   }
   __device__ __forceinline__ void get(float (&v)[8]) const {
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
@@ -52,8 +55,9 @@ struct FOperand<F32> {
   }
 };
 template <>
-struct FOperand<BF16> {
+struct FOperand<BF16, BF16> {
   uint4 x;
+  static __device__ __forceinline__ int first(int grp) { return grp * 8; }
   __device__ __forceinline__ void load(const uint16_t* p) { x = *(const uint4*)p; }
   __device__ __forceinline__ void get(float (&v)[8]) const {
     const uint32_t u[4] = {x.x, x.y, x.z, x.w};
@@ -104,12 +108,12 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
   const float* pa[RT];
   const typename S::T* pw[CT];
 #pragma unroll
-  for (int r = 0; r < RT; ++r) pa[r] = A + (size_t)min(m0 + r * 16 + c16, M - 1) * K + grp * 8;
+  for (int r = 0; r < RT; ++r) pa[r] = A + (size_t)min(m0 + r * 16 + c16, M - 1) * K + FOperand<F32, S>::first(grp);
 #pragma unroll
-  for (int c = 0; c < CT; ++c) pw[c] = W + (size_t)min(n0 + c * 16 + c16, N - 1) * K + grp * 8;
+  for (int c = 0; c < CT; ++c) pw[c] = W + (size_t)min(n0 + c * 16 + c16, N - 1) * K + FOperand<S, S>::first(grp);
   struct Stage {
-    FOperand<F32> a[RT];
-    FOperand<S> w[CT];
+    FOperand<F32, S> a[RT];
+    FOperand<S, S> w[CT];
   };
   auto load = [&](Stage& st, int kb) __attribute__((always_inline)) {
     const int k = min(min(kb, kl), KB - 1) * 32;
@@ -165,12 +169,42 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
 #pragma unroll
     for (int q = 1; q < kKQ; ++q) v += part[q][t][lane];
     const int n = n0 + (t % CT) * 16 + c16;
+    if constexpr (EPI == EPI_ARGMAX) {
+      // the tile's top-2 per row, into the LDS place of this wave's own first quarter
+      // (read above by this wave alone)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool fin = isfinite(v[i]), in = n < N;
+        const Top2s u = t2_row16(Top2s{(in & fin) ? v[i] : -INFINITY, in ? n : 0x7fffffff, -INFINITY,
+                                       (in & !fin) ? 1 : 0});
+        if (c16 == 0)
+          part[0][t][grp * 4 + i] = f32x4{u.v1, __int_as_float(u.i1), u.v2, __int_as_float(u.bad)};
+        const int m = m0 + (t / CT) * 16 + grp * 4 + i;
+        if (e.out && in && m < M) e.out[(size_t)m * e.ldo + n] = v[i];
+      }
+      continue;
+    }
     if (n >= N) continue;
     const float bn = bias ? S::ld(bias, n) : 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int m = m0 + (t / CT) * 16 + grp * 4 + i;
       if (m < M) f32_epilogue<S, EPI>(e, m, n, v[i] + bn);
+    }
+  }
+  if constexpr (EPI == EPI_ARGMAX) {   // the row's record of these 16 CT columns
+    lds_barrier();
+    for (int r = threadIdx.x; r < RT * 16; r += blockDim.x) {
+      const int m = m0 + r;
+      if (m >= M) continue;
+      Top2s u{-INFINITY, 0x7fffffff, -INFINITY, 0};
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        const f32x4 p = part[0][(r / 16) * CT + c][r % 16];
+        u = t2_merge(u, Top2s{p[0], __float_as_int(p[1]), p[2], __float_as_int(p[3])});
+      }
+      ((float4*)e.am_part)[(size_t)m * ((N + 63) / 64) + n0 / 64] =
+          float4{u.v1, __int_as_float(u.i1), u.v2, __int_as_float(u.bad)};
     }
   }
 }
@@ -181,6 +215,20 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(int M, int N, int K, cons
                                                        EpiArgs e) {
   __shared__ f32x4 part[kKQ][RT * CT][kWave];
   gemm_f32_tile<S, EPI, RT, CT, D>(M, N, K, A, W, bias, e, blockIdx.y * RT * 16, blockIdx.x * CT * 16, part);
+}
+
+// Heads (the LM head, or several draft heads over the same rows: blockIdx.z) with the argmax
+// epilogue: 64 columns per workgroup, one top-2 record per row.  The logits are stored only
+// where the caller asks for them; the separate argmax pass over them took 22 us per call.
+template <class S, int RT, int D>
+__global__ void __launch_bounds__(256) head_f32_kernel(int M, int N, int K, const float* A,
+                                                       const typename S::T* W, EpiArgs e) {
+  __shared__ f32x4 part[kKQ][RT * 4][kWave];
+  const int h = blockIdx.z;
+  W += (size_t)h * N * K;
+  e.am_part = (float4*)e.am_part + (size_t)h * M * ((N + 63) / 64);
+  if (e.out) e.out += (size_t)h * M * N;
+  gemm_f32_tile<S, EPI_ARGMAX, RT, 4, D>(M, N, K, A, W, nullptr, e, blockIdx.y * RT * 16, blockIdx.x * 64, part);
 }
 
 // The encoder K/V of several layers (blockIdx.z).
@@ -215,14 +263,32 @@ template <class S>
 void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
                      const EpiArgs& e, hipStream_t st) {
   if (epi == EPI_STORE) launch_f32<S, EPI_STORE>(M, N, K, A, W, bias, e, st);
-  if constexpr (sizeof(typename S::T) == 4) {
-    if (epi == EPI_RESID) launch_f32<S, EPI_RESID>(M, N, K, A, W, bias, e, st);
-    else if (epi == EPI_GELU) launch_f32<S, EPI_GELU>(M, N, K, A, W, bias, e, st);
-    else if (epi == EPI_QKV) launch_f32<S, EPI_QKV>(M, N, K, A, W, bias, e, st);
-  }
+  else if (epi == EPI_RESID) launch_f32<S, EPI_RESID>(M, N, K, A, W, bias, e, st);
+  else if (epi == EPI_GELU) launch_f32<S, EPI_GELU>(M, N, K, A, W, bias, e, st);
+  else if (epi == EPI_QKV) launch_f32<S, EPI_QKV>(M, N, K, A, W, bias, e, st);
 }
 template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
-template void launch_gemm_f32<BF16>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+
+int f32_records(int N) { return (N + 63) / 64; }
+
+template <class S>
+void launch_f32_head_argmax(int heads, int M, int N, int K, const float* A, const void* W, void* am_part,
+                            float* logits, hipStream_t st) {
+  EpiArgs e{};
+  e.am_part = am_part;
+  e.out = logits;
+  e.ldo = N;
+  const int MT = (M + 15) / 16;
+  auto go = [&](auto kernel, int rt) {
+    hipLaunchKernelGGL(kernel, dim3(f32_records(N), (MT + rt - 1) / rt, heads), dim3(256), 0, st, M, N, K, A,
+                       (const typename S::T*)W, e);
+  };
+  if (MT == 1) go(head_f32_kernel<S, 1, 3>, 1);
+  else if (MT == 2) go(head_f32_kernel<S, 2, 3>, 2);
+  else go(head_f32_kernel<S, 4, 2>, 4);
+}
+template void launch_f32_head_argmax<F32>(int, int, int, int, const float*, const void*, void*, float*, hipStream_t);
+template void launch_f32_head_argmax<BF16>(int, int, int, int, const float*, const void*, void*, float*, hipStream_t);
 
 void launch_xkv_f32(int M, int N, int K, const float* A, const XkvLayers& lay, int layers, const EpiArgs& e,
                     hipStream_t st) {
@@ -242,6 +308,7 @@ void launch_xkv_f32(int M, int N, int K, const float* A, const XkvLayers& lay, i
 constexpr int kAStages = 4;
 constexpr int kVGroupKeys = 128;   // keys per workgroup
 constexpr int kVPart = 2 + kHead;  // a partial: max, sum, 64 output lanes
+constexpr int kVMaxGroups = 16;    // of 2048 frames
 
 template <class S>
 struct AStage;
@@ -450,14 +517,26 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(int H, int d, int G, con
   const int sq = rows[m].seq;
   if (sq < 0 || !seqs[sq].valid) return;
   const float* pp = part + ((size_t)m * H + h) * G * kVPart;
+  // every group's partial requested before any is used (2048 frames are 16 groups)
+  float mg[kVMaxGroups], lg[kVMaxGroups], og[kVMaxGroups];
+#pragma unroll
+  for (int g = 0; g < kVMaxGroups; ++g) {
+    const float* p = pp + min(g, G - 1) * kVPart;
+    mg[g] = p[0];
+    lg[g] = p[1];
+    og[g] = p[2 + j];
+  }
   float M = -INFINITY;
-  for (int g = 0; g < G; ++g) M = fmaxf(M, pp[g * kVPart]);
+#pragma unroll
+  for (int g = 0; g < kVMaxGroups; ++g) M = fmaxf(M, mg[g]);
   float L = 0.f, acc = 0.f;
-  for (int g = 0; g < G; ++g) {
-    const float mg = pp[g * kVPart];
-    const float w = mg == -INFINITY ? 0.f : expf(mg - M);
-    L += w * pp[g * kVPart + 1];
-    acc += w * pp[g * kVPart + 2 + j];
+#pragma unroll
+  for (int g = 0; g < kVMaxGroups; ++g) {
+    const float w = (g >= G || mg[g] == -INFINITY) ? 0.f : expf(mg[g] - M);
+    if (g < G) {
+      L += w * lg[g];
+      acc += w * og[g];
+    }
   }
   out[(size_t)m * d + h * kHead + j] = acc / L;
 }
