@@ -30,7 +30,7 @@ __device__ __forceinline__ void lds_barrier() {
 // Against the vector-ALU product before it (32 x 64 tiles, one fma chain over K per output,
 // operands through LDS), 5 rows, us per launch: 384 x 384 and 384 x 1536 36.9 -> 5.5 on average,
 // QKV 22.2 -> 5.6, FFN-up 20.8 -> 4.6, the 51865-column LM head 35 -> 21 (3.8 TB/s); the four-layer
-// model's round at batch 1 1223 -> 508, its encoder K/V of 1500 frames 120 -> 70.  Each sum has
+// model's round at batch 1 1223 -> 508, its encoder K/V of 1500 frames 120 -> 59.  Each sum has
 // four shorter chains: the logits' error against 64 bits falls (1.2e-6 -> 0.7e-6).
 
 constexpr int kKQ = 4;   // K quarters, one wave each
@@ -91,13 +91,11 @@ __device__ __forceinline__ void f32_epilogue(const EpiArgs& e, int m, int n, flo
               kv_tile_base(e.layer, kv, pg, h, e.num_pages, e.H) + tile_off(kv, rd.slot % kTile, j), v);
       }
     }
-  } else if (EPI == EPI_XKV) {
-    const int kv = n / e.d, h = (n % e.d) / kHead, j = n % kHead;
-    S::st((typename S::T*)e.cache, cross_base(e.layer, h, e.H, e.frames_cap) + cross_off(kv, m, j), v);
   }
 }
 
-template <class S, int EPI, int RT, int CT, int D>
+// (SW: the operands swap places, so a lane's four sums run along the columns)
+template <class S, int EPI, int RT, int CT, int D, bool SW = false>
 __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* A, const typename S::T* W,
                                               const typename S::T* bias, const EpiArgs& e, int m0, int n0,
                                               f32x4 (*part)[RT * CT][kWave]) {
@@ -139,7 +137,8 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
       for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int c = 0; c < CT; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r][j], wv[c][j], acc[r][c], 0, 0, 0);
+          acc[r][c] = SW ? __builtin_amdgcn_mfma_f32_16x16x4f32(wv[c][j], av[r][j], acc[r][c], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_16x16x4f32(av[r][j], wv[c][j], acc[r][c], 0, 0, 0);
   };
   Stage st[D];
 #pragma unroll
@@ -168,6 +167,18 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
     f32x4 v = part[0][t][lane];
 #pragma unroll
     for (int q = 1; q < kKQ; ++q) v += part[q][t][lane];
+    if constexpr (EPI == EPI_XKV) {
+      // 64 columns from n0 are one head's keys (SW: four lanes of a frame per lane) or values
+      // (four frames of a lane): both are 16 contiguous bytes of the cache
+      const int nx = n0 + (t % CT) * 16 + (SW ? grp * 4 : c16), m = m0 + (t / CT) * 16 + (SW ? c16 : grp * 4);
+      const int kv = n0 >= e.d, h = (n0 - kv * e.d) / kHead, j = nx % kHead;
+      f32x4 bv;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bv[i] = bias[SW ? nx + i : nx];
+      if (m < M)
+        *(f32x4*)((float*)e.cache + cross_base(e.layer, h, e.H, e.frames_cap) + cross_off(kv, m, j)) = v + bv;
+      continue;
+    }
     const int n = n0 + (t % CT) * 16 + c16;
     if constexpr (EPI == EPI_ARGMAX) {
       // the tile's top-2 per row, into the LDS place of this wave's own first quarter
@@ -237,8 +248,10 @@ __global__ void __launch_bounds__(256) xkv_f32_kernel(int M, int N, int K, const
   __shared__ f32x4 part[kKQ][16][kWave];
   const int li = blockIdx.z;
   e.layer = lay.first + li;
-  gemm_f32_tile<F32, EPI_XKV, 4, 4, 2>(M, N, K, A, (const float*)lay.W[li], (const float*)lay.bias[li], e,
-                                       blockIdx.y * 64, blockIdx.x * 64, part);
+  const float *W = (const float*)lay.W[li], *b = (const float*)lay.bias[li];
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  if (n0 < e.d) gemm_f32_tile<F32, EPI_XKV, 4, 4, 2, true>(M, N, K, A, W, b, e, m0, n0, part);
+  else gemm_f32_tile<F32, EPI_XKV, 4, 4, 2>(M, N, K, A, W, b, e, m0, n0, part);
 }
 
 // Tile: one 16 x 16 tile per workgroup while that fills the chip less than eight times over
