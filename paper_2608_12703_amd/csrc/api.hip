@@ -126,9 +126,9 @@ Workspace carve(const ad_model_desc& d, int M, int B, int k_max, char* base) {
     w.ln = (float*)take(4 * M * D);
     w.att = (float*)take(4 * M * D);
     w.hid = (float*)take(4 * M * F);
-    w.gself = ad::attn_valu_groups(d.max_pos);
-    w.gcross = ad::attn_valu_groups(d.max_frames);
-    w.apart = (float*)take(4 * ad::attn_valu_part_floats(M, d.n_heads, std::max(w.gself, w.gcross)));
+    w.gself = ad::attn_f32_groups(d.max_pos);
+    w.gcross = ad::attn_f32_groups(d.max_frames);
+    w.apart = (float*)take(4 * ad::attn_f32_part_floats(M, d.n_heads, std::max(w.gself, w.gcross)));
     w.ampart = take(16ull * M * ad::f32_records((int)V));
   } else {
     const int Mp = w.RT * 16;
@@ -249,7 +249,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     ad::launch_gemm_f32<S>(ad::EPI_QKV, M, 3 * d, d, w.ln, lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
     {
       ProfScope ps(m, AD_PROF_SELF_ATTN, st);
-      ad::launch_self_attn_valu<S>(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gself, w.att,
+      ad::launch_self_attn_f32(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gself, w.att,
                                    s->kv.pool, s->kv.num_pages, s->kv.block_table, s->kv.pages_per_seq,
                                    w.tree, st);
     }
@@ -266,7 +266,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     }
     {
       ProfScope ps(m, AD_PROF_CROSS_ATTN, st);
-      ad::launch_cross_attn_valu<S>(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gcross, w.att,
+      ad::launch_cross_attn_f32(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gcross, w.att,
                                     s->cross.data, s->cross.frames_cap, st);
     }
     e.out = w.x; e.ldo = d;

@@ -1,5 +1,5 @@
-// Float32 matrix products (on the float32 matrix instruction) and float32 attention (vector
-// ALU): the float32 model's path, and the products with float32 activations and bf16 weights.
+// Float32 matrix products and attention on the float32 matrix instruction: the float32 model's
+// path, and the products with float32 activations and bf16 weights.
 //
 // Every output element is reduced in a fixed order that does not depend on how many
 // rows share the launch, so a row's result is the same alone or inside any batch.
@@ -309,214 +309,148 @@ void launch_xkv_f32(int M, int N, int K, const float* A, const XkvLayers& lay, i
 }
 
 // ---------------------------------------------------------------- attention
-// One block per (head, sequence, group of kVGroupKeys keys at absolute positions 0, 128,
-// 256, ...).  Queries are taken 16 at a time; a group's keys stream through LDS in
-// chunks of 64 with an online softmax per query, which leaves a partial (max, sum,
-// unnormalised output) per (row, head, group); a second kernel merges the groups in
-// group order.  A key a query may not see contributes exp(-inf) = 0; keys past every query's
-// range are staged as zeros so stale cache slots never reach the output.  Every thread
-// requests its part of a chunk (two runs of 8 keys' lanes and two runs of 8 values of
-// one lane, contiguous in both cache layouts) kAStages chunks ahead into registers.
+// One workgroup per (head, sequence, group of kGroupKeys keys at absolute positions 0, 128,
+// 256, ...), one 32-key block per wave, 16 queries at a time, on the float32 matrix
+// instruction.  As in the bf16 kernels the scores are computed transposed, S^T = K Q^T, with
+// key rows interleaved (row r of product tt is key 8 (r / 4) + 4 tt + r % 4 of the block), so a
+// lane holds eight consecutive keys of one query and its probabilities are the operand of
+// O^T = V^T P^T.  Every load of a wave's block goes out at once.  The waves' partials (max, sum,
+// unnormalised output) merge in wave order and leave one per (row, head, group); a second
+// kernel merges the groups in group order.  A key a query may not see gets probability 0 and
+// value slots at or past the sequence's keys are zeroed, so stale cache slots never reach the
+// output.
+//
+// Bound by latency: 5 rows x 1500 frames x 6 heads are 4.6 MB.  The vector-ALU kernel before
+// (64-key chunks through LDS, dot products and value sums as chains of 64 fused multiply-adds
+// per thread): cross-attention 18.0 -> 6.8 us, self-attention 11.3 -> 5.8 us per launch.
 
-constexpr int kAStages = 4;
-constexpr int kVGroupKeys = 128;   // keys per workgroup
+constexpr int kGroupKeys = 128;   // keys per workgroup
 constexpr int kVPart = 2 + kHead;  // a partial: max, sum, 64 output lanes
-constexpr int kVMaxGroups = 16;    // of 2048 frames
+constexpr int kMaxGroups = 16;     // of 2048 frames
 
-template <class S>
-struct AStage;
-template <>
-struct AStage<F32> {
-  float4 k[2][2], v[2][2];
-};
-template <>
-struct AStage<BF16> {
-  uint4 k[2], v[2];
-};
-
-// Load chunk c0 (keys c0 .. c0 + 63): piece u of this thread is key run (key tid / 8 +
-// 32 u, lanes 8 (tid % 8) ..) and value run (lane tid / 8 + 32 u, keys c0 + 8 (tid % 8) ..).
-// Keys at or past n_keys read the last key's place (the values become zeros in LDS).
-template <class S, bool CROSS>
-__device__ __forceinline__ void astage_load(AStage<S>& st, int c0, int n_keys, int layer, int h, int H,
-                                            int b, const SeqDesc& s, const typename S::T* kv,
-                                            int num_pages, const int* block_table, int pages_per_seq,
-                                            int frames_cap, int tid) {
-  constexpr bool F = sizeof(typename S::T) == 4;
-  const int last = max(n_keys - 1, 0);
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int tk = c0 + (tid >> 3) + 32 * u, jk = (tid & 7) * 8;   // key run
-    const int jv = (tid >> 3) + 32 * u, tv = c0 + (tid & 7) * 8;   // value run
-    size_t bk = 0, bv = 0;
-    if (CROSS) {
-      bk = cross_base(layer, h, H, frames_cap) + cross_off(0, s.enc_off + min(tk, last), jk);
-      bv = cross_base(layer, h, H, frames_cap) + cross_off(1, s.enc_off + min(tv, last) / 8 * 8, jv);
-    } else {
-      const int pk = min(max(block_table[(size_t)b * pages_per_seq + min(tk, last) / kTile], 0), num_pages - 1);
-      const int pv = min(max(block_table[(size_t)b * pages_per_seq + min(tv, last) / kTile], 0), num_pages - 1);
-      bk = kv_tile_base(layer, 0, pk, h, num_pages, H) + tile_off(0, min(tk, last) % kTile, jk);
-      bv = kv_tile_base(layer, 1, pv, h, num_pages, H) + tile_off(1, min(tv, last) / 8 * 8 % kTile, jv);
-    }
-    if constexpr (F) {
-      st.k[u][0] = *(const float4*)(kv + bk);
-      st.k[u][1] = *(const float4*)(kv + bk + 4);
-      st.v[u][0] = *(const float4*)(kv + bv);
-      st.v[u][1] = *(const float4*)(kv + bv + 4);
-    } else {
-      st.k[u] = *(const uint4*)(kv + bk);
-      st.v[u] = *(const uint4*)(kv + bv);
-    }
-  }
-}
-
-// Chunk c0's registers into LDS: ks[key][lane], vs[key][lane]; key and value slots at
-// or past n_keys are zeroed.
-template <class S>
-__device__ __forceinline__ void astage_put(const AStage<S>& st, int c0, int n_keys, float (*ks)[65],
-                                           float (*vs)[65], int tid) {
-  constexpr bool F = sizeof(typename S::T) == 4;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int rk = (tid >> 3) + 32 * u, jk = (tid & 7) * 8;
-    const int jv = (tid >> 3) + 32 * u, rv = (tid & 7) * 8;
-    float kx[8], vx[8];
-    if constexpr (F) {
-      const float4 a = st.k[u][0], bq = st.k[u][1], c = st.v[u][0], dq = st.v[u][1];
-      kx[0] = a.x; kx[1] = a.y; kx[2] = a.z; kx[3] = a.w; kx[4] = bq.x; kx[5] = bq.y; kx[6] = bq.z; kx[7] = bq.w;
-      vx[0] = c.x; vx[1] = c.y; vx[2] = c.z; vx[3] = c.w; vx[4] = dq.x; vx[5] = dq.y; vx[6] = dq.z; vx[7] = dq.w;
-    } else {
-      const uint32_t ku[4] = {st.k[u].x, st.k[u].y, st.k[u].z, st.k[u].w};
-      const uint32_t vu[4] = {st.v[u].x, st.v[u].y, st.v[u].z, st.v[u].w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        kx[2 * j] = bf16_to_f32(ku[j] & 0xffff);
-        kx[2 * j + 1] = bf16_to_f32(ku[j] >> 16);
-        vx[2 * j] = bf16_to_f32(vu[j] & 0xffff);
-        vx[2 * j + 1] = bf16_to_f32(vu[j] >> 16);
-      }
-    }
-    const bool kin = c0 + rk < n_keys;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      ks[rk][jk + e] = kin ? kx[e] : 0.f;
-      vs[rv + e][jv] = (c0 + rv + e < n_keys) ? vx[e] : 0.f;
-    }
-  }
-}
-
-template <class S, bool CROSS>
-__global__ void __launch_bounds__(256) attn_valu_kernel(int H, int d, int layer,
-                                                        const SeqDesc* seqs, const float* q,
-                                                        float* apart, int G, const typename S::T* kv,
-                                                        int num_pages, const int* block_table,
-                                                        int pages_per_seq, int frames_cap,
-                                                        const RowTree* tree) {
-  __shared__ float qs[16][65];
-  __shared__ float ks[64][65];
-  __shared__ float vs[64][65];
-  __shared__ float ps[16][65];
+template <bool CROSS>
+__global__ void __launch_bounds__(256) attn_f32_kernel(int H, int d, int layer, const SeqDesc* seqs,
+                                                       const float* q, float* apart, int G, const float* kv,
+                                                       int num_pages, const int* block_table,
+                                                       int pages_per_seq, int frames_cap,
+                                                       const RowTree* tree) {
+  constexpr int kW = kGroupKeys / 32, kORow = kHead + 4;
+  __shared__ float pm[kW][16], pl[kW][16];
+  __shared__ __align__(16) float po[kW][16][kORow];
   const int h = blockIdx.x, b = blockIdx.y, g = blockIdx.z, tid = threadIdx.x;
+  const int w = tid >> 6, lane = tid & 63, c16 = lane & 15, grp = lane >> 4;
   const SeqDesc s = seqs[b];
   if (!s.valid) return;
-  const int qi = tid >> 4, part = tid & 15;
-  const int n_rows = s.k + 1;
+  const int n_rows = s.k + 1, f0 = g * kGroupKeys + 32 * w;   // this wave's block
   for (int qg = 0; qg < n_rows; qg += 16) {
     const int nq = min(16, n_rows - qg);
-    lds_barrier();
-    for (int i = tid; i < 16 * 64; i += 256) {
-      const int r = i >> 6, j = i & 63;
-      qs[r][j] = r < nq ? q[(size_t)(s.row0 + qg + r) * d + h * kHead + j] : 0.f;
-    }
     // cross-attention sees frames [wlo, whi) (all frames unless a window was given);
     // self-attention every committed key and the block rows in the query's row mask
     const int lo = CROSS ? s.wlo : 0;
-    const unsigned long long tm = (!CROSS && qi < nq) ? tree[s.row0 + qg + qi].mask : 0ull;
     const int n_keys = CROSS ? s.whi : s.n + qg + nq;
-    float m_run = -INFINITY, l_run = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-    // this group's chunks: keys [max(lo, 128 g), min(128 (g + 1), n_keys)), 64-aligned
-    const int c_first = max(lo / 64 * 64, g * kVGroupKeys);
-    const int c_end = min((g + 1) * kVGroupKeys, n_keys);
-    const int nch = c_end > c_first ? (c_end - c_first + 63) / 64 : 0;
-    AStage<S> st0, st1, st2, st3;
-    // (chunks past the last one reread it; nch >= 1 whenever the loop runs)
-    auto load = [&](AStage<S>& st, int ci) {
-      astage_load<S, CROSS>(st, c_first + min(ci, max(nch - 1, 0)) * 64, n_keys, layer, h, H, b, s, kv,
-                            num_pages, block_table, pages_per_seq, frames_cap, tid);
-    };
-    load(st0, 0);
-    load(st1, 1);
-    load(st2, 2);
-    load(st3, 3);
-    // the scores, the online-softmax update and the value product of chunk c0 (in LDS)
-    auto attend = [&](int c0) __attribute__((always_inline)) {
-      float sc[4];
+    const bool active = f0 < n_keys && f0 + 32 > lo;
+    float m = -INFINITY, l = 0.f;
+    f32x4 o[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int key = part + 16 * u;
-        float acc = 0.f;
-#pragma unroll 16
-        for (int j = 0; j < 64; ++j) acc = fmaf(qs[qi][j], ks[key][j], acc);
-        const int t = c0 + key;
-        const bool see = CROSS ? (t >= lo && t < n_keys)
-                               : (t < s.n || (t < n_keys && ((tm >> (t - s.n)) & 1)));
-        sc[u] = (see && qi < nq) ? acc * 0.125f : -INFINITY;
+    for (int dt = 0; dt < 4; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (active) {
+      // keys: this lane's key row of product tt, dims 16 grp .. + 15; values: dim 16 dt + c16,
+      // keys 8 grp .. + 7
+      const float *kp[2][2], *vp[4];   // [product][dim half]
+      if (CROSS) {
+        const float* base = kv + cross_base(layer, h, H, frames_cap) +
+                            (size_t)((s.enc_off + f0) / kCrossBlock) * 2 * kCrossBlockElems + (grp * 16 + c16) * 8;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kp[u >> 1][u & 1] = base + u * 512;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) vp[dt] = base + kCrossBlockElems + dt * 512;
+      } else {
+        // (a tile past the last key's reads the last key's)
+        auto page = [&](int t) {
+          const int p = block_table[(size_t)b * pages_per_seq + min(f0 / kTile + t, (n_keys - 1) / kTile)];
+          return min(max(p, 0), num_pages - 1);
+        };
+        const int pk = page(c16 >> 3), pv = page(grp >> 1);
+        const float* kb = kv + kv_tile_base(layer, 0, pk, h, num_pages, H) +
+                          (((c16 >> 2) & 1) * 8 + (c16 & 3)) * kHead + grp * 16;
+        const float* vb = kv + kv_tile_base(layer, 1, pv, h, num_pages, H) + c16 * kTile + (grp & 1) * 8;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kp[u >> 1][u & 1] = kb + (u >> 1) * 4 * kHead + (u & 1) * 8;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) vp[dt] = vb + dt * 16 * kTile;
       }
-      float cm = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+      const float* qp = q + (size_t)(s.row0 + qg + min(c16, nq - 1)) * d + h * kHead + grp * 16;
+      f32x4 kf[2][4], vf[4][2], qf[4];
 #pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off, kWave));
-      const float m_new = fmaxf(m_run, cm);
-      const float scale = (m_new == -INFINITY) ? 1.f : expf(m_run - m_new);
-      float ls = 0.f;
+      for (int u = 0; u < 4; ++u) qf[u] = *(const f32x4*)(qp + 4 * u);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float p = (sc[u] == -INFINITY) ? 0.f : expf(sc[u] - m_new);
-        ps[qi][part + 16 * u] = p;
-        ls += p;
+      for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kf[tt][u] = *(const f32x4*)(kp[tt][u >> 1] + (u & 1) * 4);
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) vf[dt][u] = *(const f32x4*)(vp[dt] + 4 * u);
+      const unsigned long long tm = CROSS ? 0ull : tree[s.row0 + qg + min(c16, nq - 1)].mask;
+
+      f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+          st[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[tt][j >> 2][j & 3], qf[j >> 2][j & 3], st[tt], 0, 0, 0);
+      const int key0 = f0 + grp * 8;   // score e of this lane: key key0 + e
+      float sv[8], mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int t = key0 + e;
+        const bool see = CROSS ? (t >= lo && t < n_keys) : (t < s.n || (t < n_keys && ((tm >> ((t - s.n) & 63)) & 1)));
+        sv[e] = see ? st[e >> 2][e & 3] * 0.125f : -INFINITY;
+        mx = fmaxf(mx, sv[e]);
       }
+      m = rows4_max(mx);
+      float p[8], ps = 0.f;
 #pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) ls += __shfl_xor(ls, off, kWave);
-      l_run = l_run * scale + ls;
-      m_run = m_new;
-      lds_barrier();
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] *= scale;
-      for (int key = 0; key < 64; ++key) {
-        const float p = ps[qi][key];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = fmaf(p, vs[key][part * 4 + r], o[r]);
+      for (int e = 0; e < 8; ++e) {
+        p[e] = sv[e] == -INFINITY ? 0.f : expf(sv[e] - m);
+        ps += p[e];
       }
-    };
-    // chunk ci of the ring slot ST: stage it in LDS, request chunk ci + kAStages into the
-    // freed registers, attend
-#define VATT_CHUNK(ST, J)                                  \
-  {                                                        \
-    if (ci + (J) < nch) {                                  \
-      const int c0 = c_first + (ci + (J)) * 64;            \
-      lds_barrier();                                       \
-      astage_put<S>(ST, c0, n_keys, ks, vs, tid);          \
-      lds_barrier();                                       \
-      attend(c0);                                          \
-    }                                                      \
-    load(ST, ci + (J) + kAStages);                         \
-  }
-    for (int ci = 0; ci < nch; ci += kAStages) {
-      VATT_CHUNK(st0, 0)
-      VATT_CHUNK(st1, 1)
-      VATT_CHUNK(st2, 2)
-      VATT_CHUNK(st3, 3)
+      l = rows4_sum(ps);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+          o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(key0 + e < n_keys ? vf[dt][e >> 2][e & 3] : 0.f, p[e], o[dt], 0, 0, 0);
     }
-#undef VATT_CHUNK
-    // the group's partial: (max, sum, unnormalised output); a group without keys leaves
-    // (-inf, 0, 0)
+    if (qg) lds_barrier();   // the last group's partials have been read
+    if (grp == 0) {
+      pm[w][c16] = m;
+      pl[w][c16] = l;
+    }
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) *(f32x4*)&po[w][c16][dt * 16 + grp * 4] = o[dt];
+    lds_barrier();
+    // query tid / 16, dims 4 (tid % 16) .. + 3: the blocks in order
+    const int qi = tid >> 4, d4 = (tid & 15) * 4;
     if (qi < nq) {
+      float M = pm[0][qi];
+#pragma unroll
+      for (int u = 1; u < kW; ++u) M = fmaxf(M, pm[u][qi]);
+      float L = 0.f;
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < kW; ++u) {
+        const float wt = pm[u][qi] == -INFINITY ? 0.f : expf(pm[u][qi] - M);
+        L += wt * pl[u][qi];
+        acc += *(const f32x4*)&po[u][qi][d4] * wt;
+      }
       float* pp = apart + (((size_t)(s.row0 + qg + qi) * H + h) * G + g) * kVPart;
-      if (part == 0) {   // one of the row's 16 threads writes the statistics
-        pp[0] = m_run;
-        pp[1] = l_run;
+      if (d4 == 0) {
+        pp[0] = M;
+        pp[1] = L;
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) pp[2 + part * 4 + r] = o[r];
+      for (int i = 0; i < 4; ++i) pp[2 + d4 + i] = acc[i];
     }
   }
 }
@@ -531,9 +465,9 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(int H, int d, int G, con
   if (sq < 0 || !seqs[sq].valid) return;
   const float* pp = part + ((size_t)m * H + h) * G * kVPart;
   // every group's partial requested before any is used (2048 frames are 16 groups)
-  float mg[kVMaxGroups], lg[kVMaxGroups], og[kVMaxGroups];
+  float mg[kMaxGroups], lg[kMaxGroups], og[kMaxGroups];
 #pragma unroll
-  for (int g = 0; g < kVMaxGroups; ++g) {
+  for (int g = 0; g < kMaxGroups; ++g) {
     const float* p = pp + min(g, G - 1) * kVPart;
     mg[g] = p[0];
     lg[g] = p[1];
@@ -541,10 +475,10 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(int H, int d, int G, con
   }
   float M = -INFINITY;
 #pragma unroll
-  for (int g = 0; g < kVMaxGroups; ++g) M = fmaxf(M, mg[g]);
+  for (int g = 0; g < kMaxGroups; ++g) M = fmaxf(M, mg[g]);
   float L = 0.f, acc = 0.f;
 #pragma unroll
-  for (int g = 0; g < kVMaxGroups; ++g) {
+  for (int g = 0; g < kMaxGroups; ++g) {
     const float w = (g >= G || mg[g] == -INFINITY) ? 0.f : expf(mg[g] - M);
     if (g < G) {
       L += w * lg[g];
@@ -554,27 +488,21 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(int H, int d, int G, con
   out[(size_t)m * d + h * kHead + j] = acc / L;
 }
 
-int attn_valu_groups(int max_keys) { return (max_keys + kVGroupKeys - 1) / kVGroupKeys; }
+int attn_f32_groups(int max_keys) { return (max_keys + kGroupKeys - 1) / kGroupKeys; }
 
-template <class S>
-void launch_self_attn_valu(int B, int M, int H, int d, int layer, const SeqDesc* seqs, const RowDesc* rows,
-                           const float* q, float* part, int G, float* out, const void* pool, int num_pages,
-                           const int* block_table, int pages_per_seq, const RowTree* tree, hipStream_t st) {
-  hipLaunchKernelGGL((attn_valu_kernel<S, false>), dim3(H, B, G), dim3(256), 0, st, H, d, layer, seqs, q, part,
-                     G, (const typename S::T*)pool, num_pages, block_table, pages_per_seq, 0, tree);
+void launch_self_attn_f32(int B, int M, int H, int d, int layer, const SeqDesc* seqs, const RowDesc* rows,
+                          const float* q, float* part, int G, float* out, const void* pool, int num_pages,
+                          const int* block_table, int pages_per_seq, const RowTree* tree, hipStream_t st) {
+  hipLaunchKernelGGL(attn_f32_kernel<false>, dim3(H, B, G), dim3(256), 0, st, H, d, layer, seqs, q, part, G,
+                     (const float*)pool, num_pages, block_table, pages_per_seq, 0, tree);
   hipLaunchKernelGGL(attn_merge_kernel, dim3(M, H), dim3(64), 0, st, H, d, G, seqs, rows, part, out);
 }
-template <class S>
-void launch_cross_attn_valu(int B, int M, int H, int d, int layer, const SeqDesc* seqs, const RowDesc* rows,
-                            const float* q, float* part, int G, float* out, const void* cross, int frames_cap,
-                            hipStream_t st) {
-  hipLaunchKernelGGL((attn_valu_kernel<S, true>), dim3(H, B, G), dim3(256), 0, st, H, d, layer, seqs, q, part,
-                     G, (const typename S::T*)cross, 0, nullptr, 0, frames_cap, nullptr);
+void launch_cross_attn_f32(int B, int M, int H, int d, int layer, const SeqDesc* seqs, const RowDesc* rows,
+                           const float* q, float* part, int G, float* out, const void* cross, int frames_cap,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(attn_f32_kernel<true>, dim3(H, B, G), dim3(256), 0, st, H, d, layer, seqs, q, part, G,
+                     (const float*)cross, 0, nullptr, 0, frames_cap, nullptr);
   hipLaunchKernelGGL(attn_merge_kernel, dim3(M, H), dim3(64), 0, st, H, d, G, seqs, rows, part, out);
 }
-template void launch_self_attn_valu<F32>(int, int, int, int, int, const SeqDesc*, const RowDesc*, const float*, float*, int, float*, const void*, int, const int*, int, const RowTree*, hipStream_t);
-template void launch_self_attn_valu<BF16>(int, int, int, int, int, const SeqDesc*, const RowDesc*, const float*, float*, int, float*, const void*, int, const int*, int, const RowTree*, hipStream_t);
-template void launch_cross_attn_valu<F32>(int, int, int, int, int, const SeqDesc*, const RowDesc*, const float*, float*, int, float*, const void*, int, hipStream_t);
-template void launch_cross_attn_valu<BF16>(int, int, int, int, int, const SeqDesc*, const RowDesc*, const float*, float*, int, float*, const void*, int, hipStream_t);
 
 }  // namespace ad
