@@ -642,11 +642,11 @@ ad_status ad_verify_step_static(const ad_model* model, const ad_step* s, void* s
 }
 
 // ad_draft_input's scratch.  float32 models: the gathered rows [B][4d], the feature
-// [B][d] and the concatenated rows [B][2d] for the VALU products.  bf16 models: the
-// matrix-core products' A operand (A-fragment order, up to 4d wide), their split-K
-// partials and the feature.
+// [B][d] and the concatenated rows [B][2d] for the float32 products.  bf16 models: the
+// matrix-core products' A operand (A-fragment order, up to 4d wide) and their split-K
+// partials.
 struct DraftInputWs {
-  size_t frag, part, feat, bytes;
+  size_t frag, part, bytes;
   int RT;
 };
 DraftInputWs draft_input_ws(const ad_model_desc& D, int B) {
@@ -661,8 +661,7 @@ DraftInputWs draft_input_ws(const ad_model_desc& D, int B) {
   w.part = align256((size_t)w.RT * 16 * 4 * d * 4);
   const size_t parts = std::max(ad::gemm_part_floats(B, (int)d, 4 * (int)d),
                                 ad::gemm_part_floats(B, (int)d, 2 * (int)d));
-  w.feat = w.part + align256(4 * parts);
-  w.bytes = w.feat + align256(4 * d * B);
+  w.bytes = w.part + align256(4 * parts);
   return w;
 }
 
@@ -703,31 +702,28 @@ ad_status ad_draft_input(const ad_model* model, const void* w_fuse, const void* 
   (void)hipGetLastError();
   hipStream_t st = (hipStream_t)stream;
   if (D.dtype == AD_BF16) {
-    // matrix-core products: A operand in fragment order, split-K partials, then the sum
-    // of the partials plus the bias
+    // matrix-core products: A operand in fragment order, split-K partials; the second
+    // operand's kernel sums the first product's partials, a row kernel the second's
     const DraftInputWs w = draft_input_ws(D, batch);
     char* base = (char*)workspace;
     uint16_t* frag = (uint16_t*)(base + w.frag);
     float* part = (float*)(base + w.part);
-    float* feat = (float*)(base + w.feat);
-    auto product = [&](int K, const void* W, const void* bias, float* dst) {
+    auto product = [&](int K, const void* W) {
       ad::GemmArgs g{};
       g.M = batch; g.N = d; g.K = K; g.RT = w.RT; g.A = frag; g.W = (const uint16_t*)W;
       g.packed = 0; g.part = part;
       ad::launch_gemm_mfma(ad::EPI_PARTIAL, g, st);
-      ad::launch_sum_partials_bias(batch, d, ad::gemm_splits(d, K), part, bias, dst, st);
     };
-    const float* f = feature;
     if (taps) {
       ad::launch_draft_gather_taps_frag(batch, d, layout, k_max, cu_rows, accept_len, rows, taps,
                                         hidden, frag, w.RT, st);
-      product(4 * d, w_fuse, b_fuse, feat);
-      f = feat;
+      product(4 * d, w_fuse);
     }
-    ad::launch_draft_concat_frag(batch, d, f, model->p[P_TOK], tokens, token_stride, token_index,
-                                 frag, w.RT, st);
-    product(2 * d, w_in, b_in, out);
-    if (anchor) ad::launch_draft_window(batch, anchor, enc_len, half_window, window, st);
+    ad::launch_draft_concat_frag(batch, d, feature, taps ? ad::gemm_splits(d, 4 * d) : 0, part, b_fuse,
+                                 model->p[P_TOK], tokens, token_stride, token_index, frag, w.RT, anchor,
+                                 enc_len, half_window, window, st);
+    product(2 * d, w_in);
+    ad::launch_sum_partials_bias(batch, d, ad::gemm_splits(d, 2 * d), part, b_in, out, st);
     return check_hip("ad_draft_input");
   }
   float* taps4 = (float*)workspace;

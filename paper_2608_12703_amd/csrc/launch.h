@@ -271,9 +271,12 @@ void launch_draft_window(int B, const int* anchor, const int* enc_len, int half,
 void launch_draft_gather_taps_frag(int B, int d, int layout, int k_max, const int* cu_rows,
                                    const int* accept_len, int rows, const float* taps,
                                    const float* hidden, uint16_t* frag, int RT, hipStream_t st);
-void launch_draft_concat_frag(int B, int d, const float* feat, const void* tok_emb,
-                              const int* tokens, int token_stride, const int* token_index,
-                              uint16_t* frag, int RT, hipStream_t st);
+// (f_b: feat's row, or with nsplit > 0 the split sum of P [nsplit][B][d] plus bias; anchor, when
+// given, writes the windows)
+void launch_draft_concat_frag(int B, int d, const float* feat, int nsplit, const float* P, const void* bias,
+                              const void* tok_emb, const int* tokens, int token_stride, const int* token_index,
+                              uint16_t* frag, int RT, const int* anchor, const int* enc_len, int half,
+                              int* window, hipStream_t st);
 // out[m][n] = sum_s P[s][m][n] (split order) + bias[n], float32 rows.
 void launch_sum_partials_bias(int M, int N, int nsplit, const float* P, const void* bias, float* out,
                               hipStream_t st);
