@@ -389,19 +389,20 @@ __global__ void __launch_bounds__(512) gemm_mfma_kernel(GemmArgs g) {
     }
 }
 
-// LM head (argmax epilogue, unsplit) with 16 row tiles and 256 columns per workgroup:
+// LM head (argmax epilogue, unsplit) with 4 RW row tiles and 256 columns per workgroup:
 // at the verify block's 224 rows the 406 column tiles of the vocabulary then fit one
 // round of 203 workgroups (128 columns per workgroup take two rounds).  Eight waves, each
-// with 4 row tiles x 8 column tiles; both operands through three-stage LDS rings filled
-// by direct loads two steps ahead (144 KB).  Every output's sums run in the same order
-// as in gemm_mfma_kernel, and the per-64-column top-2 records land in the same slots.
-template <bool PACKED>
+// with RW row tiles x 8 column tiles; both operands through three-stage LDS rings filled
+// by direct loads two steps ahead (120 or 144 KB, one workgroup per CU).  Every output's sums
+// run in the same order as in gemm_mfma_kernel, and the per-64-column top-2 records land in
+// the same slots.
+template <int RW, bool PACKED>
 __global__ void __launch_bounds__(512) lm_head_kernel(GemmArgs g) {
-  constexpr int RTC = 16, RW = 4, CT = 8, NA = RTC / 4;
+  constexpr int RTC = 4 * RW, CT = 8, NA = RTC / 4;
   __shared__ uint4 sa0[RTC * 128], sa1[RTC * 128], sa2[RTC * 128];
   __shared__ uint4 sw0[2 * 512], sw1[2 * 512], sw2[2 * 512];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int rg = w & 3, ch = w >> 2;   // row group (4 row tiles), 128-column half
+  const int rg = w & 3, ch = w >> 2;   // row group (RW row tiles), 128-column half
   const int c16 = lane & 15, grp = lane >> 4;
 
   // (column group of 256, row chunk), numbered so each XCD holds a contiguous id range
@@ -833,11 +834,16 @@ static void launch_one(GemmArgs g, hipStream_t st) {
   if (launch_reg_any<EPI>(g, st)) return;
   const int rtc = gemm_rtc(g.M, g.N, g.S);
   g.mchunks = mchunks_of(g.M, rtc);
-  if (EPI == EPI_ARGMAX && rtc == 16 && g.ntiles * g.mchunks > kMaxWGs &&
-      (g.ntiles + 1) / 2 * g.mchunks <= kMaxWGs) {
+  if (EPI == EPI_ARGMAX && rtc == 16 && g.ntiles * g.mchunks > kMaxWGs) {
+    // 256 columns per workgroup and the rows in as few chunks as 16 row tiles allow, 12 or 16
+    // row tiles each (51866 columns, us, against 128-column workgroups: 224 rows 65 / 76; 352
+    // rows, 2 chunks of 12, 110 / 160; 390 rows, 2 of 16, 135 / 162)
+    const int MT = (g.M + 15) / 16, rw = (MT + g.mchunks - 1) / g.mchunks <= 12 ? 3 : 4;
     const dim3 grid((g.ntiles + 1) / 2 * g.mchunks);
-    if (g.packed) hipLaunchKernelGGL(lm_head_kernel<true>, grid, dim3(512), 0, st, g);
-    else hipLaunchKernelGGL(lm_head_kernel<false>, grid, dim3(512), 0, st, g);
+    if (rw == 3 && g.packed) hipLaunchKernelGGL((lm_head_kernel<3, true>), grid, dim3(512), 0, st, g);
+    else if (rw == 3) hipLaunchKernelGGL((lm_head_kernel<3, false>), grid, dim3(512), 0, st, g);
+    else if (g.packed) hipLaunchKernelGGL((lm_head_kernel<4, true>), grid, dim3(512), 0, st, g);
+    else hipLaunchKernelGGL((lm_head_kernel<4, false>), grid, dim3(512), 0, st, g);
     return;
   }
   const dim3 grid(g.ntiles * g.S * g.mchunks);

@@ -37,11 +37,14 @@ def _run(cfg, plist, encs, tokens, pack):
     ("bf16", 192, 384, 1003, (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 81, 96, 97, 112), True),
     ("bf16", 192, 384, 1003, (1, 33, 81), False),
     ("bf16", 1280, 5120, 517, (16, 17, 49, 80, 81, 112), True),
+    # the 256-column LM head: 12 and 16 row tiles per workgroup, one and two row chunks
+    ("bf16", 128, 128, 33001, (97, 112, 192, 193, 272, 385), True),
+    ("bf16", 128, 128, 33001, (97, 272), False),
     ("f32", 192, 384, 33001, (1, 16, 17, 32, 33, 49), False),
     ("f32", 64, 64, 1003, (1, 17, 33), False),
 ])
 def test_rows_do_not_depend_on_the_launch(dtype, d, ffn, vocab, rows, pack):
-    top = 200 if dtype == "bf16" else 70    # 13 and 5 row tiles
+    top = 400 if max(rows) > 200 else 200 if dtype == "bf16" else 70    # 25, 13 and 5 row tiles
     cfg = Config(name="rows", n_layers=1, d_model=d, n_heads=d // 64, d_ffn=ffn, vocab=vocab, dtype=dtype,
                  batch=top, k=0, frames=FRAMES, seed=21)
     params = synth.make_params(cfg)
