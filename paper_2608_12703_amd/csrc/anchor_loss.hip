@@ -195,12 +195,11 @@ __device__ __forceinline__ void q_operands(const QRaw& r, bf16x8 (&qh)[2], bf16x
 // Softmax statistics (max, sum of exp(score - max)) of every (row, head) over all valid
 // frames.  Four waves take interleaved 32-frame blocks, two blocks in flight per wave;
 // their partials merge in order.
-__global__ void __launch_bounds__(kLossThreads) aloss_stats_kernel(LossArgs a) {
-  __shared__ float2 part[4][kWave];
-  const int h = blockIdx.x, b = blockIdx.y, tile = blockIdx.z;
+__device__ __forceinline__ void stats_tile(const LossArgs& a, int h, int b, int tile, int tid,
+                                           float2 (*part)[kWave]) {
   int T, off;
   if (!seq_frames(a, b, T, off)) return;
-  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave, c16 = lane & 15, grp = lane >> 4;
+  const int w = tid / kWave, lane = tid % kWave, c16 = lane & 15, grp = lane >> 4;
   const int r = tile * 16 + c16;
   const int row = b * a.R + min(r, a.R - 1);
   bf16x8 qh[2], ql[2];
@@ -232,19 +231,24 @@ __global__ void __launch_bounds__(kLossThreads) aloss_stats_kernel(LossArgs a) {
   }
   part[w][lane] = float2{m, l};
   __syncthreads();
-  if (threadIdx.x < 16) {
-    const int rr = tile * 16 + threadIdx.x;
+  if (tid < 16) {
+    const int rr = tile * 16 + tid;
     float M = -INFINITY;
     for (int ww = 0; ww < 4; ++ww)
-      for (int g = 0; g < 4; ++g) M = fmaxf(M, part[ww][g * 16 + threadIdx.x].x);
+      for (int g = 0; g < 4; ++g) M = fmaxf(M, part[ww][g * 16 + tid].x);
     float L = 0.f;
     for (int ww = 0; ww < 4; ++ww)
       for (int g = 0; g < 4; ++g) {
-        const float2 p = part[ww][g * 16 + threadIdx.x];
+        const float2 p = part[ww][g * 16 + tid];
         if (p.x != -INFINITY) L += p.y * __expf(p.x - M);
       }
     if (rr < a.R) a.stats[(size_t)(b * a.R + rr) * a.H + h] = float2{M, L};
   }
+}
+
+__global__ void __launch_bounds__(kLossThreads) aloss_stats_kernel(LossArgs a) {
+  __shared__ float2 part[4][kWave];
+  stats_tile(a, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, part);
 }
 
 // Head-averaged attention over one 128-frame chunk: four waves take interleaved heads
@@ -465,15 +469,37 @@ __global__ void __launch_bounds__(kLossThreads) aloss_dq_kernel(LossArgs a) {
   }
 }
 
+// Smooth-L1 (beta = 1) feature term of one row (and its gradient, weight 0.5 included).
+template <int THREADS>
+__device__ __forceinline__ void feature_row(const LossArgs& a, int row, float* red) {
+  const int tid = threadIdx.x;
+  const bool tv = a.rowflag[row] & 2;
+  const float* p = a.feat + (size_t)row * a.d;
+  const float* q = a.feat_target + (size_t)row * a.d;
+  float* dp = a.out_dfeat ? a.out_dfeat + (size_t)row * a.d : nullptr;
+  const float gscale = tv ? 0.5f / ((float)a.counts[1] * (float)a.d) : 0.f;
+  float s = 0.f;
+  for (int j = tid; j < a.d; j += THREADS) {
+    const float e = p[j] - q[j];
+    const float ae = fabsf(e);
+    if (tv) s += ae < 1.f ? 0.5f * e * e : ae - 0.5f;
+    if (dp) dp[j] = fminf(fmaxf(e, -1.f), 1.f) * gscale;
+  }
+  s = block_sum<THREADS / kWave>(s, red);
+  if (tid == 0) a.feat_row[row] = s;
+}
+__global__ void __launch_bounds__(kLossThreads) aloss_feature_kernel(LossArgs a) {
+  __shared__ float red[kLossThreads / kWave];
+  feature_row<kLossThreads>(a, blockIdx.x, red);
+}
+
 // Token cross-entropy of one row (and its gradient): logsumexp - z[y].  The row stays in
 // registers (kTokThreads threads x kTokPer values): the logits are read once and the
 // gradient written once.  Up to 52 Ki logits, 512 threads x 102 values, two workgroups
 // share a CU (one's loads overlap the other's arithmetic); up to 64 Ki, 1024 x 64.
 template <int VEC, int kTokThreads, int kTokPer>
-__global__ void __launch_bounds__(kTokThreads) __attribute__((amdgpu_waves_per_eu(kTokThreads == 512 ? 4 : 1)))
-aloss_token_reg_kernel(LossArgs a) {
-  __shared__ float red[kTokThreads / kWave];
-  const int row = blockIdx.x, tid = threadIdx.x;
+__device__ __forceinline__ void token_row(const LossArgs& a, int row, float* red) {
+  const int tid = threadIdx.x;
   const float* z = a.logits + (size_t)row * a.V;
   float* dz = a.out_dlogits ? a.out_dlogits + (size_t)row * a.V : nullptr;
   if (!(a.rowflag[row] & 2)) {
@@ -530,6 +556,35 @@ aloss_token_reg_kernel(LossArgs a) {
   }
 }
 
+template <int VEC, int kTokThreads, int kTokPer>
+__global__ void __launch_bounds__(kTokThreads) __attribute__((amdgpu_waves_per_eu(kTokThreads == 512 ? 4 : 1)))
+aloss_token_reg_kernel(LossArgs a) {
+  __shared__ float red[kTokThreads / kWave];
+  token_row<VEC, kTokThreads, kTokPer>(a, blockIdx.x, red);
+}
+
+// Token rows (with their feature rows) and the softmax statistics in one launch, dealt evenly
+// over the block ids: the rows stream the logits and their gradient from memory while the
+// statistics re-read keys from L2, so the two overlap (12 x 128 positions, 51866 logits, 1500
+// frames, 20 heads: 117 + 42 + 9 us in launches of their own, 145 together).  A statistics workgroup takes two 16-row tiles of one head
+// and sequence, four waves each (a tile past the last one stores nothing).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+aloss_token_stats_kernel(LossArgs a, int nstats) {
+  __shared__ float red[512 / kWave], fred[512 / kWave];
+  __shared__ float2 part[2][4][kWave];
+  const long long bid = blockIdx.x, total = gridDim.x;
+  const int before = (int)(bid * nstats / total);      // statistics workgroups below this one
+  if ((int)((bid + 1) * nstats / total) > before) {
+    const int pairs = ((a.R + 15) / 16 + 1) / 2, half = threadIdx.x / kLossThreads;
+    const int tile = before % pairs * 2 + half, hb = before / pairs;
+    stats_tile(a, hb % a.H, hb / a.H, tile, threadIdx.x % kLossThreads, part[half]);
+    return;
+  }
+  const int row = (int)bid - before;
+  if (a.feat) feature_row<512>(a, row, fred);
+  token_row<2, 512, 102>(a, row, red);
+}
+
 // The same for larger vocabularies: two passes over the logits.
 __global__ void __launch_bounds__(kLossThreads) aloss_token_kernel(LossArgs a) {
   __shared__ float red[2][kLossThreads / kWave];
@@ -583,26 +638,6 @@ __global__ void __launch_bounds__(kLossThreads) aloss_token_kernel(LossArgs a) {
   }
 }
 
-// Smooth-L1 (beta = 1) feature term of one row (and its gradient, weight 0.5 included).
-__global__ void __launch_bounds__(kLossThreads) aloss_feature_kernel(LossArgs a) {
-  __shared__ float red[kLossThreads / kWave];
-  const int row = blockIdx.x, tid = threadIdx.x;
-  const bool tv = a.rowflag[row] & 2;
-  const float* p = a.feat + (size_t)row * a.d;
-  const float* q = a.feat_target + (size_t)row * a.d;
-  float* dp = a.out_dfeat ? a.out_dfeat + (size_t)row * a.d : nullptr;
-  const float gscale = tv ? 0.5f / ((float)a.counts[1] * (float)a.d) : 0.f;
-  float s = 0.f;
-  for (int j = tid; j < a.d; j += kLossThreads) {
-    const float e = p[j] - q[j];
-    const float ae = fabsf(e);
-    if (tv) s += ae < 1.f ? 0.5f * e * e : ae - 0.5f;
-    if (dp) dp[j] = fminf(fmaxf(e, -1.f), 1.f) * gscale;
-  }
-  s = block_sum<kLossThreads / kWave>(s, red);
-  if (tid == 0) a.feat_row[row] = s;
-}
-
 // Each row's alignment cross-entropy: the sum of its block partials (one wave per row,
 // a fixed butterfly).
 __global__ void __launch_bounds__(kLossThreads) aloss_rowsum_kernel(LossArgs a) {
@@ -653,22 +688,32 @@ void launch_anchordraft_loss(const LossArgs& a, hipStream_t st) {
   const int tiles = (a.R + 15) / 16;
   hipLaunchKernelGGL(aloss_prep_kernel, dim3((a.M + 3) / 4), dim3(kLossThreads), 0, st, a);
   hipLaunchKernelGGL(aloss_count_kernel, dim3(1), dim3(1024), 0, st, a);
-  if (a.xq) {
+  // the register-resident token rows share a launch with the statistics (and take the feature
+  // rows with them); other vocabularies keep a launch of their own
+  const bool shared = a.xq && a.logits && a.V <= 512 * 102 && a.V % 2 == 0;
+  if (shared) {
+    const int nstats = a.H * a.B * ((tiles + 1) / 2);
+    hipLaunchKernelGGL(aloss_token_stats_kernel, dim3(a.M + nstats), dim3(512), 0, st, a, nstats);
+  } else if (a.xq) {
     hipLaunchKernelGGL(aloss_stats_kernel, dim3(a.H, a.B, tiles), dim3(kLossThreads), 0, st, a);
+  }
+  if (a.xq) {
     hipLaunchKernelGGL(aloss_abar_kernel, dim3((a.nchunk + kAbarBlocks - 1) / kAbarBlocks, a.B, tiles),
                        dim3(kLossThreads), 0, st, a);
     if (a.out_dxq)
       hipLaunchKernelGGL(aloss_dq_kernel, dim3(a.H, a.B, tiles), dim3(kLossThreads), 0, st, a);
   }
-  if (a.logits && a.V <= 512 * 102 && a.V % 2 == 0)
-    hipLaunchKernelGGL((aloss_token_reg_kernel<2, 512, 102>), dim3(a.M), dim3(512), 0, st, a);
-  else if (a.logits && a.V <= 1024 * 64 && a.V % 2 == 0)
-    hipLaunchKernelGGL((aloss_token_reg_kernel<2, 1024, 64>), dim3(a.M), dim3(1024), 0, st, a);
-  else if (a.logits && a.V <= 1024 * 64)
-    hipLaunchKernelGGL((aloss_token_reg_kernel<1, 1024, 64>), dim3(a.M), dim3(1024), 0, st, a);
-  else if (a.logits)
-    hipLaunchKernelGGL(aloss_token_kernel, dim3(a.M), dim3(kLossThreads), 0, st, a);
-  if (a.feat) hipLaunchKernelGGL(aloss_feature_kernel, dim3(a.M), dim3(kLossThreads), 0, st, a);
+  if (a.logits && !shared) {
+    if (a.V <= 512 * 102 && a.V % 2 == 0)
+      hipLaunchKernelGGL((aloss_token_reg_kernel<2, 512, 102>), dim3(a.M), dim3(512), 0, st, a);
+    else if (a.V <= 1024 * 64 && a.V % 2 == 0)
+      hipLaunchKernelGGL((aloss_token_reg_kernel<2, 1024, 64>), dim3(a.M), dim3(1024), 0, st, a);
+    else if (a.V <= 1024 * 64)
+      hipLaunchKernelGGL((aloss_token_reg_kernel<1, 1024, 64>), dim3(a.M), dim3(1024), 0, st, a);
+    else
+      hipLaunchKernelGGL(aloss_token_kernel, dim3(a.M), dim3(kLossThreads), 0, st, a);
+  }
+  if (a.feat && !shared) hipLaunchKernelGGL(aloss_feature_kernel, dim3(a.M), dim3(kLossThreads), 0, st, a);
   if (a.xq) hipLaunchKernelGGL(aloss_rowsum_kernel, dim3((a.M + 3) / 4), dim3(kLossThreads), 0, st, a);
   hipLaunchKernelGGL(aloss_final_kernel, dim3(1), dim3(1024), 0, st, a);
 }
