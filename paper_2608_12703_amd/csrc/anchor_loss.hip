@@ -257,7 +257,8 @@ __global__ void __launch_bounds__(kLossThreads) aloss_stats_kernel(LossArgs a) {
 // finishes block w: each row's cross-entropy partial, and g = -q / (H Abar) into
 // workspace (0 where q is 0 or the row has no alignment).
 constexpr int kAbarBlocks = 4;
-__global__ void __launch_bounds__(kLossThreads) aloss_abar_kernel(LossArgs a) {
+// (three waves per SIMD: 78 -> 70 us)
+__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(3))) aloss_abar_kernel(LossArgs a) {
   __shared__ float part[4][kAbarBlocks][8][kWave];
   const int chunk = blockIdx.x, b = blockIdx.y, tile = blockIdx.z;
   int T, off;
@@ -353,10 +354,13 @@ __global__ void __launch_bounds__(kLossThreads) aloss_abar_kernel(LossArgs a) {
 // Gradient of lambda L_anchor for the query rows (0 for rows without an alignment).
 // Four waves take interleaved 32-frame blocks, two in flight per wave (keys and the
 // row's Abar values of the block); partials merge in wave order.
-__global__ void __launch_bounds__(kLossThreads) aloss_dq_kernel(LossArgs a) {
-  __shared__ uint16_t kt[4][kCrossBlock * kKtStride];   // per wave: one block's keys, [key][dim]
-  __shared__ float xy[4][2][kHead][16];                  // per wave: X, Y partials [dim][row]
+// (Three waves per SIMD, the keys' tile in the place of the later partials: 81 -> 78 us; four spill,
+// 113 us.)
+__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(3))) aloss_dq_kernel(LossArgs a) {
+  // per wave: X, Y partials [dim][row]; before that, one block's keys, [key][dim]
+  __shared__ __align__(16) float xy[4][2][kHead][16];
   __shared__ float cpart[4][16];
+  static_assert(kCrossBlock * kKtStride * 2 <= 2 * kHead * 16 * 4, "a wave's keys fit its partials' place");
   const int h = blockIdx.x, b = blockIdx.y, tile = blockIdx.z;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave, c16 = lane & 15, grp = lane >> 4;
   int T, off;
@@ -379,7 +383,7 @@ __global__ void __launch_bounds__(kLossThreads) aloss_dq_kernel(LossArgs a) {
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) X[dt] = Y[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float cs = 0.f;
-  uint16_t* myk = kt[w];
+  uint16_t* myk = (uint16_t*)&xy[w][0][0][0];
   // this lane's two key rows of the tile (products tt = 0, 1) and its 16 dims
   const int kA = 8 * (c16 >> 2) + (c16 & 3);
   struct BlkRaw {

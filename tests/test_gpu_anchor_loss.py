@@ -261,3 +261,40 @@ def test_full_size_objective_sampled_against_oracle():
         print(f"  utterance {b}: row losses within 2e-5; query gradient: max error {err.max():.2e} of "
               f"max, {frac:.4f} of (row, head) pairs past 5e-4")
         assert frac <= 0.01 and err.max() <= 5e-3
+
+
+@pytest.mark.parametrize("R", [5, 16, 17, 37])
+def test_terms_do_not_depend_on_which_passes_share_a_launch(R):
+    """With query rows and an even vocabulary the token rows, feature rows and softmax
+    statistics share one launch (row tiles in pairs); alone they have launches of their own.
+    Every pass computes the same sums either way, except the feature term's (512 instead of 256
+    partial sums per row: float32 sums of d = 128 terms, 1e-6 relative)."""
+    cfg = UNIT
+    params, dparams = synth.make_params(cfg), synth.make_draft_params(cfg)
+    B, Ts = 3, [300, 157, 41]
+    dcfg, sess = _draft_session(cfg, params, dparams, B, R, Ts)
+    sess.prefill_encoder([synth.make_encoder(cfg, b, T) for b, T in enumerate(Ts)])
+    M, d, V, dev = B * R, cfg.d_model, cfg.vocab, "cuda"
+    center, targets, logits, feat, feat_target = _inputs(cfg, B, R, Ts, 9)
+    T = lambda a, dt=torch.float32: torch.tensor(np.asarray(a), dtype=dt, device=dev)
+    xq = T(np.random.default_rng(1).standard_normal((M, d)) * 8)
+    center, targets = T(center, torch.int32), T(targets, torch.int32)
+    logits, feat, feat_target = T(logits), T(feat), T(feat_target)
+    ws = torch.empty(ad.anchordraft_loss_workspace_size(sess.model, B, R), dtype=torch.uint8, device=dev)
+    z = lambda *s: torch.zeros(*s, device=dev)
+    err = torch.zeros(1, dtype=torch.int32, device=dev)
+
+    def run(align, token):
+        out = z(4), z(M), z(M, d), z(M, V), z(M, d)
+        ad.anchordraft_loss(sess.model, sess.cross_struct() if align else None, 0, B, R, xq if align else None,
+                            center if align else None, SIGMA, LAM, logits if token else None, targets,
+                            feat if token else None, feat_target if token else None, out[0],
+                            out[1] if align else None, out[2] if align else None, out[3] if token else None,
+                            out[4] if token else None, err, ws)
+        return out
+    both, align, token = run(True, True), run(True, False), run(False, True)
+    assert int(err.item()) == 0
+    assert torch.equal(both[1], align[1]) and torch.equal(both[2], align[2])
+    assert torch.equal(both[3], token[3]) and torch.equal(both[4], token[4])
+    assert both[0][1] == token[0][1] and both[0][3] == align[0][3]
+    assert abs(float(both[0][2] - token[0][2])) <= 1e-6 * float(token[0][2])
