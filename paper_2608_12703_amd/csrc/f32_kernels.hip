@@ -5,6 +5,7 @@
 // rows share the launch, so a row's result is the same alone or inside any batch.
 #include "common.h"
 #include "launch.h"
+#include "top2.h"
 
 namespace ad {
 

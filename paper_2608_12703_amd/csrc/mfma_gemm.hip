@@ -21,6 +21,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "top2.h"
 
 namespace ad {
 

@@ -333,3 +333,45 @@ def test_large_v3_tree_step_sampled():
     np.testing.assert_array_equal(kv_post[:, :, n:].view(np.uint32),
                                   kv_pre[:, :, [n + u for u in path]].view(np.uint32))
     assert int(res_c["kv_len"][b_s]) == n + a + 1
+
+
+def test_descriptors_of_64_row_blocks():
+    """A lane of the descriptor pass holds a block row: 64-row trees (a chain, a star, random)
+    beside one-row blocks.  Chain against the linear block and padded against packed by bits, a
+    random tree against the oracle, and faults that only the last row holds."""
+    cfg = UNIT
+    params = synth.make_params(cfg)
+    wl = synth.make_step_workload(cfg)
+    model = oracle_model(cfg, params)
+    rng = np.random.default_rng(7)
+    trees = [[-1] + list(range(63)), random_tree(rng, 64), [-1], [-1] + [0] * 63, random_tree(rng, 63)]
+    blocks = tree_blocks(cfg, model, wl, trees, rng)
+
+    def run(layout, parents, toks=blocks):
+        s = device_session(cfg, params, wl, layout=layout, k_max=63)
+        s.step(toks, parents=parents)
+        r = s.results()
+        return r, [r["logits"][[s.row_of(b, i) for i in range(len(trees[b]))]] for b in range(wl.batch)]
+
+    rp, lp = run(ad.AD_PADDED, trees)
+    rk, lk = run(ad.AD_PACKED, trees)
+    _, line = run(ad.AD_PADDED, None)
+    assert rp["err"] == 0 and rk["err"] == 0
+    np.testing.assert_array_equal(rp["path"], rk["path"])
+    for b in range(wl.batch):
+        np.testing.assert_array_equal(lp[b].view(np.uint32), lk[b].view(np.uint32))
+    for b in (0, 2):
+        np.testing.assert_array_equal(lp[b].view(np.uint32), line[b].view(np.uint32))
+    st = oracle_state(cfg, model, 1, int(wl.n[1]), int(wl.T[1]), int(wl.t0[1]))
+    ref = od.forward_block(model, st, blocks[1], parents=trees[1])
+    assert float(np.max(np.abs(lp[1] - ref.logits))) <= LOGIT_TOL[cfg.dtype]
+    bad_tree = [list(t) for t in trees]
+    bad_tree[3][63] = 63
+    bad_token = [b.copy() for b in blocks]
+    bad_token[1][63] = cfg.vocab
+    for layout in (ad.AD_PADDED, ad.AD_PACKED):
+        for err, gone, (r, got) in ((ad.AD_ERR_TREE, 3, run(layout, bad_tree)),
+                                    (ad.AD_ERR_TOKEN, 1, run(layout, trees, bad_token))):
+            assert r["err"] == err and r["accept_len"][gone] == -1
+            for b in set(range(wl.batch)) - {gone}:
+                np.testing.assert_array_equal(got[b].view(np.uint32), lp[b].view(np.uint32))
