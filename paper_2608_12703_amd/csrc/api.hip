@@ -244,9 +244,9 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
   for (int l = 0; l < D.n_layers; ++l) {
     e.layer = l;
     // self-attention sublayer
-    ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN1_G), lp(m, l, LN1_B), w.ln, st);
     e.out = w.q; e.ldo = d; e.cache = s->kv.pool;
-    ad::launch_gemm_f32<S>(ad::EPI_QKV, M, 3 * d, d, w.ln, lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
+    ad::launch_ln_gemm_f32(ad::EPI_QKV, M, 3 * d, d, w.x, lp(m, l, LN1_G), lp(m, l, LN1_B), w.ln,
+                           lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
     {
       ProfScope ps(m, AD_PROF_SELF_ATTN, st);
       ad::launch_self_attn_f32(s->batch, M, H, d, l, w.seqs, w.rows, w.q, w.apart, w.gself, w.att,
@@ -256,9 +256,9 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     e.out = w.x; e.ldo = d;
     ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_O), lp(m, l, B_O), e, st);
     // cross-attention sublayer
-    ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN2_G), lp(m, l, LN2_B), w.ln, st);
     e.out = w.q; e.ldo = d;
-    ad::launch_gemm_f32<S>(ad::EPI_STORE, M, d, d, w.ln, lp(m, l, W_XQ), lp(m, l, B_XQ), e, st);
+    ad::launch_ln_gemm_f32(ad::EPI_STORE, M, d, d, w.x, lp(m, l, LN2_G), lp(m, l, LN2_B), w.ln,
+                           lp(m, l, W_XQ), lp(m, l, B_XQ), e, st);
     if (l == s->anchor_layer) {
       (void)hipMemcpyAsync(w.q_anchor, w.q, sizeof(float) * M * d, hipMemcpyDeviceToDevice, st);
       if (s->out_xq)
@@ -272,9 +272,9 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     e.out = w.x; e.ldo = d;
     ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_XO), lp(m, l, B_XO), e, st);
     // feed-forward sublayer
-    ad::launch_layernorm<S>(M, d, w.x, lp(m, l, LN3_G), lp(m, l, LN3_B), w.ln, st);
     e.out = w.hid; e.ldo = F;
-    ad::launch_gemm_f32<S>(ad::EPI_GELU, M, F, d, w.ln, lp(m, l, W_1), lp(m, l, B_1), e, st);
+    ad::launch_ln_gemm_f32(ad::EPI_GELU, M, F, d, w.x, lp(m, l, LN3_G), lp(m, l, LN3_B), w.ln,
+                           lp(m, l, W_1), lp(m, l, B_1), e, st);
     e.out = w.x; e.ldo = d;
     ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, F, w.hid, lp(m, l, W_2), lp(m, l, B_2), e, st);
     copy_taps(s, l, w.x, M, d, st);

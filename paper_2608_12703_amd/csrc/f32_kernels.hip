@@ -5,6 +5,7 @@
 // rows share the launch, so a row's result is the same alone or inside any batch.
 #include "common.h"
 #include "launch.h"
+#include "row_stats.h"
 #include "top2.h"
 
 namespace ad {
@@ -95,14 +96,27 @@ __device__ __forceinline__ void f32_epilogue(const EpiArgs& e, int m, int n, flo
   }
 }
 
-// (SW: the operands swap places, so a lane's four sums run along the columns)
-template <class S, int EPI, int RT, int CT, int D, bool SW = false>
+// (SW: the operands swap places, so a lane's four sums run along the columns.  LN, float32 and
+// RT = 1 only: A holds the rows before their LayerNorm; each wave takes the statistics of four
+// of the 16 rows, and the rows are normalised as they enter the product.)
+template <class S, int EPI, int RT, int CT, int D, bool SW = false, bool LN = false>
 __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* A, const typename S::T* W,
                                               const typename S::T* bias, const EpiArgs& e, int m0, int n0,
-                                              f32x4 (*part)[RT * CT][kWave]) {
+                                              f32x4 (*part)[RT * CT][kWave], const float* ln_g = nullptr,
+                                              const float* ln_b = nullptr) {
+  static_assert(!LN || (RT == 1 && sizeof(typename S::T) == 4), "one row tile of float32");
   const int lane = threadIdx.x & 63, c16 = lane & 15, grp = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KB = K / 32, kb0 = (w * KB) / kKQ, kb1 = ((w + 1) * KB) / kKQ, kl = max(kb1 - 1, kb0);
+  // the statistics' rows are requested first: loads return in order, so the operands below stay
+  // in flight while the statistics are taken
+  f32x4 xr[kRowParts];
+  if constexpr (LN) {
+    const float* row = A + (size_t)min(m0 + 4 * w + grp, M - 1) * K;
+#pragma unroll
+    for (int t = 0; t < kRowParts; ++t) xr[t] = row_part(row, K, c16, t);
+    asm volatile("" ::: "memory");   // the operands' loads stay behind these
+  }
   // rows and columns past the matrix read its last (those results are never stored)
   const float* pa[RT];
   const typename S::T* pw[CT];
@@ -113,6 +127,7 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
   struct Stage {
     FOperand<F32, S> a[RT];
     FOperand<S, S> w[CT];
+    FOperand<F32, S> g, b;   // LN: the scale and shift of the same k
   };
   auto load = [&](Stage& st, int kb) __attribute__((always_inline)) {
     const int k = min(min(kb, kl), KB - 1) * 32;
@@ -120,7 +135,12 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
     for (int c = 0; c < CT; ++c) st.w[c].load(pw[c] + k);
 #pragma unroll
     for (int r = 0; r < RT; ++r) st.a[r].load(pa[r] + k);
+    if constexpr (LN) {
+      st.g.load(ln_g + FOperand<F32, S>::first(grp) + k);
+      st.b.load(ln_b + FOperand<F32, S>::first(grp) + k);
+    }
   };
+  float2 rs{0.f, 1.f};
   f32x4 acc[RT][CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
@@ -132,6 +152,13 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
     for (int r = 0; r < RT; ++r) st.a[r].get(av[r]);
 #pragma unroll
     for (int c = 0; c < CT; ++c) st.w[c].get(wv[c]);
+    if constexpr (LN) {
+      float gv[8], bv[8];
+      st.g.get(gv);
+      st.b.get(bv);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) av[0][j] = normalised(av[0][j], rs, gv[j], bv[j]);
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -144,6 +171,14 @@ __device__ __forceinline__ void gemm_f32_tile(int M, int N, int K, const float* 
   Stage st[D];
 #pragma unroll
   for (int u = 0; u < D; ++u) load(st[u], kb0 + u);
+  if constexpr (LN) {
+    __shared__ float2 stats[16];
+    __builtin_amdgcn_sched_barrier(0);
+    const float2 q = row_stats(xr, K);
+    if (c16 == 0) stats[4 * w + grp] = q;
+    lds_barrier();
+    rs = stats[c16];
+  }
   int kb = kb0;
   for (int it = 0; it < (kb1 - kb0 - 1) / D; ++it) {
 #pragma unroll
@@ -229,6 +264,18 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(int M, int N, int K, cons
   gemm_f32_tile<S, EPI, RT, CT, D>(M, N, K, A, W, bias, e, blockIdx.y * RT * 16, blockIdx.x * CT * 16, part);
 }
 
+// The product of rows that it normalises itself (A: the residual stream, at most kRowStatsMax
+// wide), where a LayerNorm launch of its own costs more than it computes: 5 rows of 384, the
+// launch 3.9 us, the product 4.2-5.6 us alone and 5.0-6.2 us with its LayerNorm (statistics by a
+// wave per four rows with 64-lane butterflies instead of 16 lanes per row: 7.3-8.5 us).
+template <class S, int EPI, int D>
+__global__ void __launch_bounds__(256) ln_gemm_f32_kernel(int M, int N, int K, const float* A, const float* g,
+                                                          const float* b, const typename S::T* W,
+                                                          const typename S::T* bias, EpiArgs e) {
+  __shared__ f32x4 part[kKQ][1][kWave];
+  gemm_f32_tile<S, EPI, 1, 1, D, false, true>(M, N, K, A, W, bias, e, blockIdx.y * 16, blockIdx.x * 16, part, g, b);
+}
+
 // Heads (the LM head, or several draft heads over the same rows: blockIdx.z) with the argmax
 // epilogue: 64 columns per workgroup, one top-2 record per row.  The logits are stored only
 // where the caller asks for them; the separate argmax pass over them took 22 us per call.
@@ -282,6 +329,27 @@ void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W
   else if (epi == EPI_QKV) launch_f32<S, EPI_QKV>(M, N, K, A, W, bias, e, st);
 }
 template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+
+// LayerNorm, then the product.  One launch where the product runs 16 x 16 tiles and a wave holds
+// a row (each workgroup normalises its own 16 rows again, so larger tiles and wider rows keep
+// the LayerNorm kernel and its float32 rows `ln`); the results are the same bits.  (A model's
+// parameters are 16-byte aligned.)
+void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
+                        const void* W, const void* bias, const EpiArgs& e, hipStream_t st) {
+  const int MT = (M + 15) / 16, NT = (N + 15) / 16;
+  if ((long long)MT * NT > 2048 || K > kRowStatsMax) {
+    launch_layernorm<F32>(M, K, x, g, b, ln, st);
+    launch_gemm_f32<F32>(epi, M, N, K, ln, W, bias, e, st);
+    return;
+  }
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(NT, MT), dim3(256), 0, st, M, N, K, x, (const float*)g, (const float*)b,
+                       (const float*)W, (const float*)bias, e);
+  };
+  if (epi == EPI_STORE) go(ln_gemm_f32_kernel<F32, EPI_STORE, 3>);
+  else if (epi == EPI_GELU) go(ln_gemm_f32_kernel<F32, EPI_GELU, 3>);
+  else if (epi == EPI_QKV) go(ln_gemm_f32_kernel<F32, EPI_QKV, 3>);
+}
 
 int f32_records(int N) { return (N + 63) / 64; }
 

@@ -93,6 +93,9 @@ void launch_f32_head_argmax(int heads, int M, int N, int K, const float* A, cons
 template <class S>
 void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
                       const EpiArgs& e, hipStream_t st);
+// LayerNorm of the rows x, then the product (EPI_STORE, EPI_GELU or EPI_QKV); ln holds M x K floats.
+void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
+                        const void* W, const void* bias, const EpiArgs& e, hipStream_t st);
 
 // Cross-attention keys / values of a bf16 model's encoder states on the matrix cores, for
 // `layers` consecutive layers (at most kXkvLayers): cache <- enc A [M][K] W[i] [N][K]^T +

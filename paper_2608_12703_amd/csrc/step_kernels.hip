@@ -3,6 +3,7 @@
 // the draft-head helpers.
 #include "common.h"
 #include "launch.h"
+#include "row_stats.h"
 #include "top2.h"
 
 namespace ad {
@@ -130,6 +131,15 @@ __global__ void __launch_bounds__(256) layernorm_kernel(int d, const float* x,
   __shared__ float red[4];
   const int m = blockIdx.x;
   const float* xr = x + (size_t)m * d;
+  if (d <= kRowStatsMax) {   // every 16 lanes take the row's statistics, no barrier
+    f32x4 xs[kRowParts];
+#pragma unroll
+    for (int t = 0; t < kRowParts; ++t) xs[t] = row_part(xr, d, threadIdx.x % 16, t);
+    const float2 rs = row_stats(xs, d);
+    for (int j = threadIdx.x; j < d; j += 256)
+      out[(size_t)m * d + j] = normalised(xr[j], rs, S::ld(g, j), S::ld(b, j));
+    return;
+  }
   float s = 0.f;
   for (int j = threadIdx.x; j < d; j += 256) s += xr[j];
   const float mean = block_sum<4>(s, red) / (float)d;

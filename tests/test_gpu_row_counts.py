@@ -42,6 +42,9 @@ def _run(cfg, plist, encs, tokens, pack):
     ("bf16", 128, 128, 33001, (97, 272), False),
     ("f32", 192, 384, 33001, (1, 16, 17, 32, 33, 49), False),
     ("f32", 64, 64, 1003, (1, 17, 33), False),
+    # LayerNorm inside the product and as a launch of its own (the widest fused row; the up
+    # product of 257 rows and the QKV product of 400 have more than 2048 tiles)
+    ("f32", 512, 2048, 515, (1, 17, 256, 257), False),
 ])
 def test_rows_do_not_depend_on_the_launch(dtype, d, ffn, vocab, rows, pack):
     top = 400 if max(rows) > 200 else 200 if dtype == "bf16" else 70    # 25, 13 and 5 row tiles
