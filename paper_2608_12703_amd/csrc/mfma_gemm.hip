@@ -17,6 +17,8 @@
 // the product (attention, or residual + LayerNorm) sums the partials in split order.
 // The split count depends on the weight shape only, so a row's result never depends
 // on how many other rows share the launch.
+// Launches with too few output tiles to fill the chip that way run gemm_reg_kernel: one
+// wave per few tiles, both operands straight into registers, the same sums in the same order.
 #include <algorithm>
 
 #include "common.h"
@@ -732,8 +734,9 @@ int gemm_splits(int N, int K) {
 // 6.29 (packed) / 7.22 (padded) against 6.52 / 7.41 ms, the verify step unchanged.  The
 // row tiling never changes a row's sums (same K order, same split order).
 // When no tile fits (the LM head's 406 column tiles), 16 row tiles, or 4 when that
-// needs no more row chunks (up to 64 rows, the draft block's 32): a 4-row-tile K step
-// costs a third of a 16-row-tile one (draft step 198 -> 156 us at batch 32).
+// needs no more row chunks (49 to 64 rows; fewer run the register-direct product): a
+// 4-row-tile K step costs a third of a 16-row-tile one (a draft step of 32 rows, before
+// that product took it, 198 -> 156 us).
 constexpr int kMaxWGsRows = 256;
 int gemm_rtc(int M, int N, int S) {
   const int ntiles = (N + kNT - 1) / kNT;
