@@ -18,6 +18,9 @@ HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed float32 instructions stay off: scalar float code only
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # kernels view one LDS buffer through several types (bf16 key tiles and float partials in
+    # one place): accesses of different types must keep their order
+    "-fno-strict-aliasing",
     "-Wall", "-Wno-unused-function",
 ]
 

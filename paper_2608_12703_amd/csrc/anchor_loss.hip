@@ -357,7 +357,8 @@ __global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_
 // (Three waves per SIMD, the keys' tile in the place of the later partials: 81 -> 78 us; four spill,
 // 113 us.)
 __global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(3))) aloss_dq_kernel(LossArgs a) {
-  // per wave: X, Y partials [dim][row]; before that, one block's keys, [key][dim]
+  // per wave: X, Y partials [dim][row]; before that, one block's keys, [key][dim] (the partials'
+  // float stores follow the keys' 16-bit reads: the library is built without strict aliasing)
   __shared__ __align__(16) float xy[4][2][kHead][16];
   __shared__ float cpart[4][16];
   static_assert(kCrossBlock * kKtStride * 2 <= 2 * kHead * 16 * 4, "a wave's keys fit its partials' place");
