@@ -734,9 +734,9 @@ int gemm_splits(int N, int K) {
 // 6.29 (packed) / 7.22 (padded) against 6.52 / 7.41 ms, the verify step unchanged.  The
 // row tiling never changes a row's sums (same K order, same split order).
 // When no tile fits (the LM head's 406 column tiles), 16 row tiles, or 4 when that
-// needs no more row chunks (49 to 64 rows; fewer run the register-direct product): a
-// 4-row-tile K step costs a third of a 16-row-tile one (a draft step of 32 rows, before
-// that product took it, 198 -> 156 us).
+// needs no more row chunks (up to 64 rows): a 4-row-tile K step costs a third of a
+// 16-row-tile one (a draft step of 32 rows, before the register-direct product took its
+// head, 198 -> 156 us).
 constexpr int kMaxWGsRows = 256;
 int gemm_rtc(int M, int N, int S) {
   const int ntiles = (N + kNT - 1) / kNT;
@@ -786,17 +786,39 @@ static void launch_rtc(const GemmArgs& g, dim3 grid, hipStream_t st) {
 // in brackets): 32 rows, FFN-up [640] 1x1 7.2, 1x2 8.1; QKV [960] 1x1 5.7, 1x2 5.0; 64 rows,
 // d x d [1600] 1x2 3.9, 1x4 3.9; QKV [1920] 1x2 6.6, 1x4 6.1; 80 rows, QKV [2400] 1x4 8.6,
 // 2x4 8.0; 112 rows, FFN-down [3360] 1x4 13.3, 2x4 10.4, LDS kernel 13.0; 160 rows, d x d
-// [4000] 2x4 5.3, LDS 6.3; QKV [4800] 2x4 10.6, LDS 10.4.
+// [4000] 2x4 5.3, LDS 6.3; QKV [4800] 2x4 10.6, LDS 10.4.  Over d 128 to 4096 and 1 to 352 rows
+// the six products of a layer together are at most 1.02 times what the LDS kernel takes.
+//
+// LM head (64 columns per wave, a top-2 record): the register-direct product pays where the LDS
+// kernel needs a second round of workgroups, that is past 256 column tiles of 128 (32768
+// columns); with one workgroup per CU or fewer its longer chain per wave loses, the more the
+// more row tiles share it.  us, register-direct / LDS, weights from HBM (a 1 GB fill before
+// each pass) and, in brackets, from the caches:
+//   1 row tile, d 1280   16001 columns 26.9 / 25.0   33001 37.6 / 51.4 (16.8 / 26.6)   51866 54.4 / 60.2 (23.2 / 27.6)
+//               d 384     5003 10.9 / 11.2             25003 13.3 / 13.5 (8.2 / 9.2)     51866 20.2 / 23.1 (11.4 / 14.0)
+//   2, d 1280            16001 33.0 / 25.5 (17.6 / 15.4)   33001 41 / 52 (19.6 / 26.7)   51866 57 / 61 (25.5 / 28.0)
+//                        70001 92 / 85 (42 / 39)   100003 102 / 109 (56 / 68)   152064 135 / 132 (96 / 99)
+//   3, d 1280            16001 25.2 / 25.6 (19.0 / 15.5)   33001 46 / 54 (23 / 27)   45001 54 / 61 (26 / 28)   51866 65 / 62 (30 / 28.5)
+//   5, d 1280            16001 28 / 26 (20 / 17)   25003 40 / 44 (24 / 28)   29001 43.5 / 44.6 (24 / 28)
+//                        33001 51 / 72 (31 / 66)   51866 73 / 79 (38 / 68)
+//   4 and 7 or more row tiles: the LDS kernel, whose chunks they fill.
+// So: one row tile of tiled weights past one round of the LDS kernel, or with d <= 768 (0.86 to
+// 1.01 of it at every vocabulary; row-major weights 1.15 to 1.23); two, and one of row-major
+// weights, where the last 512-tile round of this kernel's four-wave workgroups is at least half
+// full; three up to half of the LDS kernel's second round, d >= 768 (d 384: 1.03 to 1.06 of it);
+// five and six past one round.
 struct RegTile {
   int rtw, ctw;
 };
-static RegTile reg_tile(int epi, int MT, int N, int S) {
+static RegTile reg_tile(int epi, int MT, int N, int K, int S, bool packed) {
   if (epi == EPI_ARGMAX) {
-    // 64 columns per wave (a top-2 record); 51866 columns, register-direct against LDS: 1 row
-    // tile 25.2 / 37.6 us, 2 28.5 / 37.8, 3 34.0 / 38.1, 4 39.6 / 38.0 (one chunk of four
-    // row tiles is the LDS kernel's best case), 5 47.9 / 63.0, 7 62.2 / 64.4, 10 73 / 64
-    if (MT <= 3) return {MT, 4};
-    return {MT == 5 || MT == 6 ? 3 : 0, 4};
+    const int nt = (N + kNT - 1) / kNT;
+    const bool half = (nt - 1) % 512 >= 256;
+    if (MT == 1) return {(packed ? nt > kMaxWGs || K <= 768 : half) ? 1 : 0, 4};
+    if (MT == 2) return {half ? 2 : 0, 4};
+    if (MT == 3) return {nt > kMaxWGs && nt <= 384 && K >= 768 ? 3 : 0, 4};
+    if (MT == 5 || MT == 6) return {nt > kMaxWGs ? 3 : 0, 4};
+    return {0, 4};
   }
   const long long tiles = (long long)MT * ((N + 15) / 16) * S;
   if (tiles <= 720) return {1, 1};
@@ -817,7 +839,7 @@ static void launch_reg(GemmArgs g, int waves, hipStream_t st) {
 
 template <int EPI>
 static bool launch_reg_any(const GemmArgs& g, hipStream_t st) {
-  const RegTile t = reg_tile(EPI, (g.M + 15) / 16, g.N, g.S);
+  const RegTile t = reg_tile(EPI, (g.M + 15) / 16, g.N, g.K, g.S, g.packed);
   if constexpr (EPI == EPI_ARGMAX) {
     if (t.rtw == 1) launch_reg<EPI, 1, 4, 8>(g, 4, st);
     else if (t.rtw == 2) launch_reg<EPI, 2, 4, 5>(g, 4, st);

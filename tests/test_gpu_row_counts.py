@@ -1,7 +1,10 @@
 """The projections and the LM head at the row counts where the launch changes kernel or tile.
 
 A launch with few 16 x 16 output tiles runs the register-direct product (one to eight tiles
-per wave), a larger one the LDS product, and the LM head switches at 1, 2, 3, 5-6 row tiles.
+per wave), a larger one the LDS product.  The LM head runs the register-direct product at 1, 2,
+3, 5 and 6 row tiles where the LDS product would take a second round of workgroups (33001
+columns are 258 tiles of 128; three row tiles from width 768 on), and at one row tile of tiled
+weights up to width 768; the other vocabularies here take the LDS product otherwise.
 One row per sequence: the same sequences in batches of every size must give the same bits
 (the order of a row's sums never depends on the launch), and the rows must match the oracle.
 The float32 product changes its tile by the number of 16 x 16 output tiles (the vocabulary of
@@ -37,6 +40,9 @@ def _run(cfg, plist, encs, tokens, pack):
     ("bf16", 192, 384, 1003, (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 81, 96, 97, 112), True),
     ("bf16", 192, 384, 1003, (1, 33, 81), False),
     ("bf16", 1280, 5120, 517, (16, 17, 49, 80, 81, 112), True),
+    # the register-direct LM head at every row tile count that it takes
+    ("bf16", 768, 128, 33001, (1, 16, 17, 32, 33, 48, 49, 65, 80, 81, 96, 97), True),
+    ("bf16", 768, 128, 33001, (16, 32, 48, 96), False),
     # the 256-column LM head: 12 and 16 row tiles per workgroup, one and two row chunks
     ("bf16", 128, 128, 33001, (97, 112, 192, 193, 272, 385), True),
     ("bf16", 128, 128, 33001, (97, 272), False),
