@@ -862,15 +862,23 @@ static void launch_one(GemmArgs g, hipStream_t st) {
   g.mchunks = mchunks_of(g.M, rtc);
   if (EPI == EPI_ARGMAX && rtc == 16 && g.ntiles * g.mchunks > kMaxWGs) {
     // 256 columns per workgroup and the rows in as few chunks as 16 row tiles allow, 12 or 16
-    // row tiles each (51866 columns, us, against 128-column workgroups: 224 rows 65 / 76; 352
-    // rows, 2 chunks of 12, 110 / 160; 390 rows, 2 of 16, 135 / 162)
+    // row tiles each, where rounds of one workgroup per CU make that the faster: one of 12 (16)
+    // row tiles takes 1.31 to 1.46 (1.59 to 1.77) of the time of one of 128 columns x 16 row tiles
+    // (d 384 to 2048, 16001 to 51866 columns, 256 to 1600 rows).  us at d 1280, against
+    // 128-column workgroups: 51866 columns, 224 rows 65 / 76; 390 rows, 2 rounds for 4, 139 /
+    // 167; 576 rows, 3 of 12 row tiles for 5, 171 / 218; 704 rows, 3 for 5, 217 / 222; 1600 rows,
+    // 6 for 12, 440 / 511; 33001 columns, 390 rows, 2 for 3, 131 / 116
     const int MT = (g.M + 15) / 16, rw = (MT + g.mchunks - 1) / g.mchunks <= 12 ? 3 : 4;
-    const dim3 grid((g.ntiles + 1) / 2 * g.mchunks);
-    if (rw == 3 && g.packed) hipLaunchKernelGGL((lm_head_kernel<3, true>), grid, dim3(512), 0, st, g);
-    else if (rw == 3) hipLaunchKernelGGL((lm_head_kernel<3, false>), grid, dim3(512), 0, st, g);
-    else if (g.packed) hipLaunchKernelGGL((lm_head_kernel<4, true>), grid, dim3(512), 0, st, g);
-    else hipLaunchKernelGGL((lm_head_kernel<4, false>), grid, dim3(512), 0, st, g);
-    return;
+    const int wgs = (g.ntiles + 1) / 2 * g.mchunks, r256 = (wgs + kMaxWGs - 1) / kMaxWGs;
+    const int r128 = (g.ntiles * g.mchunks + kMaxWGs - 1) / kMaxWGs;
+    if (rw == 3 ? 29 * r256 <= 20 * r128 : 7 * r256 <= 4 * r128) {
+      const dim3 grid(wgs);
+      if (rw == 3 && g.packed) hipLaunchKernelGGL((lm_head_kernel<3, true>), grid, dim3(512), 0, st, g);
+      else if (rw == 3) hipLaunchKernelGGL((lm_head_kernel<3, false>), grid, dim3(512), 0, st, g);
+      else if (g.packed) hipLaunchKernelGGL((lm_head_kernel<4, true>), grid, dim3(512), 0, st, g);
+      else hipLaunchKernelGGL((lm_head_kernel<4, false>), grid, dim3(512), 0, st, g);
+      return;
+    }
   }
   const dim3 grid(g.ntiles * g.S * g.mchunks);
   if (g.packed) {

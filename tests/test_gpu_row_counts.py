@@ -43,7 +43,9 @@ def _run(cfg, plist, encs, tokens, pack):
     # the register-direct LM head at every row tile count that it takes
     ("bf16", 768, 128, 33001, (1, 16, 17, 32, 33, 48, 49, 65, 80, 81, 96, 97), True),
     ("bf16", 768, 128, 33001, (16, 32, 48, 96), False),
-    # the 256-column LM head: 12 and 16 row tiles per workgroup, one and two row chunks
+    # the 256-column LM head: 12 and 16 row tiles per workgroup, one and two row chunks (33001
+    # columns x 385 rows stay with 128-column workgroups)
+    ("bf16", 128, 128, 51865, (272, 385), True),
     ("bf16", 128, 128, 33001, (97, 112, 192, 193, 272, 385), True),
     ("bf16", 128, 128, 33001, (97, 272), False),
     ("f32", 192, 384, 33001, (1, 16, 17, 32, 33, 49), False),
