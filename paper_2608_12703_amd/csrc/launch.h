@@ -101,7 +101,7 @@ void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void
 // `layers` consecutive layers (at most kXkvLayers): cache <- enc A [M][K] W[i] [N][K]^T +
 // bias[i] in the cross-K/V layout of layer first + i (N = 2d, M a multiple of 32).  a_packed:
 // enc as written by launch_pack_rows; w_packed: W tiled by launch_pack_weight; otherwise
-// row-major.
+// row-major (row-major states: one layer).
 constexpr int kXkvLayers = 64;   // layers of one launch (1 KB of kernel arguments)
 struct XkvLayers {
   const void* W[kXkvLayers];      // of the model's type

@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(512) xkv_mfma_kernel(int M, int N, int K, cons
   const int nwg = gridDim.x, bid = blockIdx.x;
   const int x = bid & 7, q8 = nwg >> 3, r8 = nwg & 7;
   const int all = x * q8 + min(x, r8) + (bid >> 3);
-  const int li = all / (NT * MB), lin = all - li * (NT * MB);
+  const int li = APK ? all / (NT * MB) : 0, lin = all - li * (NT * MB);   // (row-major states: one layer)
   const int gc = (NT + 1) / 2;
   const int g = lin / (MB * gc), rem = lin - g * MB * gc;
   const int gw = min(gc, NT - g * gc);
@@ -247,16 +247,28 @@ static void launch_tiles(int M, int N, int K, const uint16_t* A, bool a_packed, 
 
 void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const XkvLayers& lay, int layers,
                      bool w_packed, uint16_t* cache, int H, int d, int frames_cap, hipStream_t st) {
-  // Large tiles read half the operand bytes per product; small ones fill the chip when there
-  // are few rounds of 256 workgroups.  Small / large, us (large tiles in brackets): staged
-  // states, 12 layers of d 768 [396] 76 / 92, 16 of d 640 [600] 86 / 121, 32 of d 1280 [1860]
-  // 373 / 368, [3720] 693 / 647; row-major states, whose gathered loads small tiles double,
-  // one layer of d 1280 [60] 21 / 57, [240] 58 / 61, [710] 165 / 141.
+  // Large tiles read half the operand bytes per product, small ones fill the chip.  Either kind
+  // takes as long as its rounds of 256 workgroups, each a fixed part and KB 32-wide steps, and a
+  // large tile past the last frame stores its `rest` of up to 224 frames one element at a time.
+  // In units of a small tile's step of row-major states (0.28 us): small, a round KB + 10;
+  // large, 2.8 KB + 40 and 0.7 rest with staged states, 2.4 KB + 24 and 0.5 rest with row-major
+  // ones (whose gathered loads small tiles double).  Fitted to 592 launches (d 64 to 3072, 32 to
+  // 24064 frames, 1 to 4 layers): the choice is within 1.02 of large tiles everywhere and within
+  // 1.1 of the faster kind in all but one (1.26).  us, small / large (rounds): row-major states,
+  // one layer, d 1280, 1504 frames (1, 1) 20 / 57; 5632 (4, 1) 54 / 37; 8064 (5, 2) 69 / 91;
+  // 12032 (8, 2) 106 / 74; d 2048, 2816 (3, 1) 62 / 47; staged (with the
+  // staging copy), d 1280, four layers of 1504 (4, 1) 49 / 64; one of 24064 (15, 4) 194 / 182;
+  // d 768, four of 12032 (18, 5) 130 / 119
   const long long large = (long long)((N + 255) / 256) * ((M + 255) / 256) * layers;
-  if (large > (a_packed ? 1500 : 256))
-    launch_tiles<2>(M, N, K, A, a_packed, lay, layers, w_packed, cache, H, d, frames_cap, st);
-  else
+  const long long small = (long long)((N + 127) / 128) * ((M + 127) / 128) * layers;
+  const long long rl = (large + 255) / 256, rs = (small + 255) / 256;
+  const int KB = K / 32, rest = M % 256;
+  const long long t_small = 10 * rs * (KB + 10);
+  const long long t_large = a_packed ? rl * (28 * KB + 400) + 7 * rest : rl * (24 * KB + 240) + 5 * rest;
+  if (t_small <= t_large)
     launch_tiles<1>(M, N, K, A, a_packed, lay, layers, w_packed, cache, H, d, frames_cap, st);
+  else
+    launch_tiles<2>(M, N, K, A, a_packed, lay, layers, w_packed, cache, H, d, frames_cap, st);
 }
 
 void launch_pack_rows(const uint16_t* A, int M, int K, uint16_t* P, hipStream_t st) {

@@ -84,11 +84,13 @@ def test_prefill_matches_oracle_large_v3():
 
 
 @pytest.mark.parametrize("n_layers,frames", [
-    (1, [1500] * 5),           # 300 tiles of 256 x 256, row-major encoder states
+    (1, [1500] * 5),           # 128 x 128 tiles, row-major encoder states, five rounds
+    (1, [1500] * 4),           # 256 x 256 tiles, row-major states, the last ones partial
+    (2, [1500] * 4 + [384]),   # 256 x 256 tiles of staged states and of the last layer's
     (66, [31, 64]),            # more layers than one launch takes
 ])
 def test_prefill_tile_sizes_and_layer_launches(n_layers, frames):
-    cfg = Config(name="unit_prefill_tiles", n_layers=n_layers, d_model=1280 if n_layers == 1 else 192,
-                 n_heads=20 if n_layers == 1 else 3, d_ffn=256, vocab=100, dtype="bf16", batch=len(frames), k=1,
+    cfg = Config(name="unit_prefill_tiles", n_layers=n_layers, d_model=1280 if n_layers <= 2 else 192,
+                 n_heads=20 if n_layers <= 2 else 3, d_ffn=256, vocab=100, dtype="bf16", batch=len(frames), k=1,
                  frames=max(frames), seed=12)
     _check(cfg, frames, layers=sorted({0, n_layers // 2, n_layers - 2 if n_layers > 1 else 0, n_layers - 1}))
