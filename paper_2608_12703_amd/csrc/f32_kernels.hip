@@ -333,12 +333,15 @@ template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*
 
 // LayerNorm, then the product.  One launch where the product runs 16 x 16 tiles and a wave holds
 // a row (each workgroup normalises its own 16 rows again, so larger tiles and wider rows keep
-// the LayerNorm kernel and its float32 rows `ln`); the results are the same bits.  (A model's
-// parameters are 16-byte aligned.)
+// the LayerNorm kernel and its float32 rows `ln`); the results are the same bits.  Past d 384 a
+// wave's K quarter is longer than its ring of three steps and the repeated LayerNorms show: up to
+// six row tiles only.  us a step of four layers, one launch / two: d 384, 16 rows 215 / 251, 128
+// 295 / 331, 400 633 / 648; d 512, 16 rows 245 / 269, 80 324 / 328, 96 350 / 346, 128 392 / 379,
+// 256 664 / 592.  (A model's parameters are 16-byte aligned.)
 void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
                         const void* W, const void* bias, const EpiArgs& e, hipStream_t st) {
   const int MT = (M + 15) / 16, NT = (N + 15) / 16;
-  if ((long long)MT * NT > 2048 || K > kRowStatsMax) {
+  if ((long long)MT * NT > 2048 || K > kRowStatsMax || (K > 384 && MT > 6)) {
     launch_layernorm<F32>(M, K, x, g, b, ln, st);
     launch_gemm_f32<F32>(epi, M, N, K, ln, W, bias, e, st);
     return;
