@@ -257,8 +257,11 @@ __global__ void __launch_bounds__(kLossThreads) aloss_stats_kernel(LossArgs a) {
 // finishes block w: each row's cross-entropy partial, and g = -q / (H Abar) into
 // workspace (0 where q is 0 or the row has no alignment).
 constexpr int kAbarBlocks = 4;
-// (three waves per SIMD: 78 -> 70 us)
-__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(3))) aloss_abar_kernel(LossArgs a) {
+// (EU waves per SIMD.  Three, 168 registers and one spilled: 12 x 128 positions, 1500 frames, 20
+// heads 78 -> 70 us; 8 x 128 positions of 800 frames, the whole objective 140 -> 122.  One, 192
+// registers: launch_anchordraft_loss.)
+template <int EU>
+__global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(EU))) aloss_abar_kernel(LossArgs a) {
   __shared__ float part[4][kAbarBlocks][8][kWave];
   const int chunk = blockIdx.x, b = blockIdx.y, tile = blockIdx.z;
   int T, off;
@@ -694,17 +697,29 @@ void launch_anchordraft_loss(const LossArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(aloss_prep_kernel, dim3((a.M + 3) / 4), dim3(kLossThreads), 0, st, a);
   hipLaunchKernelGGL(aloss_count_kernel, dim3(1), dim3(1024), 0, st, a);
   // the register-resident token rows share a launch with the statistics (and take the feature
-  // rows with them); other vocabularies keep a launch of their own
-  const bool shared = a.xq && a.logits && a.V <= 512 * 102 && a.V % 2 == 0;
+  // rows with them); other vocabularies keep a launch of their own.  Past two statistics
+  // workgroups per CU (512 threads each) their rounds only hide behind a long token stream, or
+  // pay where the statistics are long themselves: 12 x 128 positions, 20 heads (960 of them), us
+  // of the objective, shared / separate: 1000 logits, 50 frames 103 / 98, 400 119 / 117, 1500
+  // 187 / 199; 20000 logits, 800 frames 176 / 172, 1500 213 / 222; 51866 logits, 50 frames 203 /
+  // 204, 1500 281 / 306.  Up to 512 of them it is 0.82 to 1.04 of separate launches.
+  const int nstats = a.H * a.B * ((tiles + 1) / 2);
+  const bool shared = a.xq && a.logits && a.V <= 512 * 102 && a.V % 2 == 0 &&
+                      (nstats <= 512 || a.V > 32768 || a.frames_cap >= 1024 * a.B);
   if (shared) {
-    const int nstats = a.H * a.B * ((tiles + 1) / 2);
     hipLaunchKernelGGL(aloss_token_stats_kernel, dim3(a.M + nstats), dim3(512), 0, st, a, nstats);
   } else if (a.xq) {
     hipLaunchKernelGGL(aloss_stats_kernel, dim3(a.H, a.B, tiles), dim3(kLossThreads), 0, st, a);
   }
   if (a.xq) {
-    hipLaunchKernelGGL(aloss_abar_kernel, dim3((a.nchunk + kAbarBlocks - 1) / kAbarBlocks, a.B, tiles),
-                       dim3(kLossThreads), 0, st, a);
+    // A grid past three workgroups per CU, few of them with frames (at most one partial chunk a
+    // sequence besides the cache's whole ones), runs one wave per SIMD: 12 x 128 positions of 50
+    // frames, 1152 workgroups and 96 with frames, 25.5 against 30.9 us.
+    const dim3 grid((a.nchunk + kAbarBlocks - 1) / kAbarBlocks, a.B, tiles);
+    const long long all = (long long)grid.x * a.B * tiles;
+    const long long some = (a.frames_cap / (kAbarBlocks * kCrossBlock) + (long long)a.B) * tiles;
+    if (all > 768 && some <= 512) hipLaunchKernelGGL(aloss_abar_kernel<1>, grid, dim3(kLossThreads), 0, st, a);
+    else hipLaunchKernelGGL(aloss_abar_kernel<3>, grid, dim3(kLossThreads), 0, st, a);
     if (a.out_dxq)
       hipLaunchKernelGGL(aloss_dq_kernel, dim3(a.H, a.B, tiles), dim3(kLossThreads), 0, st, a);
   }
