@@ -4,7 +4,8 @@ Paper, section "Correction and Cost", paragraph "AnchorDraft Training Objective"
 appendix "Training Correction with AnchorDraft" (eq. anchordraft-supp).
 * The same query rows, centres, logits and features on both sides (three utterances of
   300, 157 and 41 frames, 37 padded rows each: three 16-row tiles with a ragged one,
-  unaligned rows and rows without a next token): the four terms, every row's alignment
+  unaligned rows and rows without a next token; and two of 50 and 33 frames with 530 and 4100
+  rows, the other launch choices): the four terms, every row's alignment
   cross-entropy and the three gradients.
 * Bad centres and targets raise their error bits and drop out of the sums.
 * End to end: the draft block's forward over a block of training positions on the GPU
@@ -98,10 +99,14 @@ def _check(got, want: al.ObjectiveOut, B, R, center_ok=None):
         assert e <= 1e-5 * s
 
 
-def test_objective_matches_oracle_on_the_same_inputs():
+@pytest.mark.parametrize("B,R,Ts", [
+    (3, 37, [300, 157, 41]),
+    (2, 530, [50, 33]),      # a grid mostly without frames: one wave per SIMD in the head average
+    (2, 4100, [50, 33]),     # statistics past two workgroups per CU: token rows in their own launch
+])
+def test_objective_matches_oracle_on_the_same_inputs(B, R, Ts):
     cfg = UNIT
     params, dparams = synth.make_params(cfg), synth.make_draft_params(cfg)
-    B, R, Ts = 3, 37, [300, 157, 41]
     dcfg, sess = _draft_session(cfg, params, dparams, B, R, Ts)
     encs = [synth.make_encoder(cfg, b, T) for b, T in enumerate(Ts)]
     sess.prefill_encoder(encs)
