@@ -222,7 +222,6 @@ void accept(const ad_step* s, const Workspace& w, const int* greedy, hipStream_t
     ad::launch_accept(s->batch, s->k_max, w.seqs, s->tokens, greedy, s->accept_len, s->out_tokens, st);
 }
 
-template <class S>
 void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipStream_t st) {
   const ad_model_desc& D = m->desc;
   const int M = s->rows, d = D.d_model, F = D.d_ffn, H = D.n_heads, V = D.vocab;
@@ -231,7 +230,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
                  s->kv.pages_per_seq, s->kv.num_pages, s->cross.enc_len, s->cross.enc_off,
                  s->cross.frames_cap, s->cross_window, s->parents, w.tree};
   ad::launch_prep(a, w.seqs, w.rows, s->err_flag, st);
-  ad::launch_embed<S>(M, d, w.rows, m->p[P_TOK], m->p[P_POS], w.x, s->in_rows, st);
+  ad::launch_embed<ad::F32>(M, d, w.rows, m->p[P_TOK], m->p[P_POS], w.x, s->in_rows, st);
 
   ad::EpiArgs e{};
   e.rows = w.rows;
@@ -245,7 +244,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     e.layer = l;
     // self-attention sublayer
     e.out = w.q; e.ldo = d; e.cache = s->kv.pool;
-    ad::launch_ln_gemm_f32(ad::EPI_QKV, M, 3 * d, d, w.x, lp(m, l, LN1_G), lp(m, l, LN1_B), w.ln,
+    ad::launch_ln_gemm_f32<ad::EPI_QKV>(M, 3 * d, d, w.x, lp(m, l, LN1_G), lp(m, l, LN1_B), w.ln,
                            lp(m, l, W_QKV), lp(m, l, B_QKV), e, st);
     {
       ProfScope ps(m, AD_PROF_SELF_ATTN, st);
@@ -254,10 +253,10 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
                                    w.tree, st);
     }
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_O), lp(m, l, B_O), e, st);
+    ad::launch_gemm_f32<ad::EPI_RESID>(M, d, d, w.att, lp(m, l, W_O), lp(m, l, B_O), e, st);
     // cross-attention sublayer
     e.out = w.q; e.ldo = d;
-    ad::launch_ln_gemm_f32(ad::EPI_STORE, M, d, d, w.x, lp(m, l, LN2_G), lp(m, l, LN2_B), w.ln,
+    ad::launch_ln_gemm_f32<ad::EPI_STORE>(M, d, d, w.x, lp(m, l, LN2_G), lp(m, l, LN2_B), w.ln,
                            lp(m, l, W_XQ), lp(m, l, B_XQ), e, st);
     if (l == s->anchor_layer) {
       (void)hipMemcpyAsync(w.q_anchor, w.q, sizeof(float) * M * d, hipMemcpyDeviceToDevice, st);
@@ -270,25 +269,25 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
                                     s->cross.data, s->cross.frames_cap, st);
     }
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, d, w.att, lp(m, l, W_XO), lp(m, l, B_XO), e, st);
+    ad::launch_gemm_f32<ad::EPI_RESID>(M, d, d, w.att, lp(m, l, W_XO), lp(m, l, B_XO), e, st);
     // feed-forward sublayer
     e.out = w.hid; e.ldo = F;
-    ad::launch_ln_gemm_f32(ad::EPI_GELU, M, F, d, w.x, lp(m, l, LN3_G), lp(m, l, LN3_B), w.ln,
+    ad::launch_ln_gemm_f32<ad::EPI_GELU>(M, F, d, w.x, lp(m, l, LN3_G), lp(m, l, LN3_B), w.ln,
                            lp(m, l, W_1), lp(m, l, B_1), e, st);
     e.out = w.x; e.ldo = d;
-    ad::launch_gemm_f32<S>(ad::EPI_RESID, M, d, F, w.hid, lp(m, l, W_2), lp(m, l, B_2), e, st);
+    ad::launch_gemm_f32<ad::EPI_RESID>(M, d, F, w.hid, lp(m, l, W_2), lp(m, l, B_2), e, st);
     copy_taps(s, l, w.x, M, d, st);
   }
   float* hidden = s->out_hidden ? s->out_hidden : w.hidden;
-  ad::launch_layernorm<S>(M, d, w.x, m->p[P_LNF_G], m->p[P_LNF_B], hidden, st);
+  ad::launch_layernorm<ad::F32>(M, d, w.x, m->p[P_LNF_G], m->p[P_LNF_B], hidden, st);
   {
     ProfScope ps(m, AD_PROF_LM_HEAD, st);
-    ad::launch_f32_head_argmax<S>(1, M, V, d, hidden, m->p[P_TOK], w.ampart, s->out_logits, st);
+    ad::launch_f32_head_argmax<ad::F32>(1, M, V, d, hidden, m->p[P_TOK], w.ampart, s->out_logits, st);
   }
   int* greedy = s->out_greedy ? s->out_greedy : w.greedy;
   ad::launch_argmax_final(M, ad::f32_records(V), w.ampart, w.rows, greedy, s->out_margin, s->err_flag, st);
   accept(s, w, greedy, st);
-  if (s->anchor_layer >= 0) ad::launch_anchor<S>(anchor_args(m, s, w), s->batch, st);
+  if (s->anchor_layer >= 0) ad::launch_anchor<ad::F32>(anchor_args(m, s, w), s->batch, st);
 }
 
 // bf16 model.  The projections write split-K partial products that the next kernel
@@ -621,7 +620,7 @@ ad_status ad_verify_step(const ad_model* model, const ad_step* s, void* stream) 
   const Workspace w = carve(D, s->rows, s->batch, s->k_max, (char*)s->workspace);
   hipStream_t st = (hipStream_t)stream;
   if (D.dtype == AD_BF16) run_step_mfma(model, s, w, st);
-  else run_step_f32<ad::F32>(model, s, w, st);
+  else run_step_f32(model, s, w, st);
   return check_hip("ad_verify_step");
 }
 
@@ -736,12 +735,12 @@ ad_status ad_draft_input(const ad_model* model, const void* w_fuse, const void* 
     ad::launch_draft_gather_taps(batch, d, layout, k_max, cu_rows, accept_len, rows, taps, hidden,
                                  taps4, st);
     e.out = feat;
-    ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
+    ad::launch_gemm_f32<ad::EPI_STORE>(batch, d, 4 * d, taps4, w_fuse, b_fuse, e, st);
     f = feat;
   }
   ad::launch_draft_concat(batch, d, f, model->p[P_TOK], tokens, token_stride, token_index, z, st);
   e.out = out;
-  ad::launch_gemm_f32<ad::F32>(ad::EPI_STORE, batch, d, 2 * d, z, w_in, b_in, e, st);
+  ad::launch_gemm_f32<ad::EPI_STORE>(batch, d, 2 * d, z, w_in, b_in, e, st);
   if (anchor) ad::launch_draft_window(batch, anchor, enc_len, half_window, window, st);
   return check_hip("ad_draft_input");
 }

@@ -306,30 +306,22 @@ __global__ void __launch_bounds__(256) xkv_f32_kernel(int M, int N, int K, const
 // Tile: one 16 x 16 tile per workgroup while that fills the chip less than eight times over
 // (the most waves for the least latency), else four column tiles and as many row tiles as
 // there are, up to four (operand bytes per product fall with the tile).
-template <class S, int EPI>
-static void launch_f32(int M, int N, int K, const float* A, const void* W, const void* bias, const EpiArgs& e,
-                       hipStream_t st) {
-  const auto* w = (const typename S::T*)W;
-  const auto* b = (const typename S::T*)bias;
+template <int EPI>
+void launch_gemm_f32(int M, int N, int K, const float* A, const void* W, const void* bias, const EpiArgs& e,
+                     hipStream_t st) {
+  const auto* w = (const float*)W;
+  const auto* b = (const float*)bias;
   const int MT = (M + 15) / 16, NT = (N + 15) / 16;
   auto go = [&](auto kernel, int rt, int ct) {
     hipLaunchKernelGGL(kernel, dim3((NT + ct - 1) / ct, (MT + rt - 1) / rt), dim3(256), 0, st, M, N, K, A, w, b, e);
   };
-  if ((long long)MT * NT <= 2048) go(gemm_f32_kernel<S, EPI, 1, 1, 4>, 1, 1);
-  else if (MT == 1) go(gemm_f32_kernel<S, EPI, 1, 4, 3>, 1, 4);
-  else if (MT == 2) go(gemm_f32_kernel<S, EPI, 2, 4, 3>, 2, 4);
-  else go(gemm_f32_kernel<S, EPI, 4, 4, 2>, 4, 4);
+  if ((long long)MT * NT <= 2048) go(gemm_f32_kernel<F32, EPI, 1, 1, 4>, 1, 1);
+  else if (MT == 1) go(gemm_f32_kernel<F32, EPI, 1, 4, 3>, 1, 4);
+  else if (MT == 2) go(gemm_f32_kernel<F32, EPI, 2, 4, 3>, 2, 4);
+  else go(gemm_f32_kernel<F32, EPI, 4, 4, 2>, 4, 4);
 }
-
-template <class S>
-void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
-                     const EpiArgs& e, hipStream_t st) {
-  if (epi == EPI_STORE) launch_f32<S, EPI_STORE>(M, N, K, A, W, bias, e, st);
-  else if (epi == EPI_RESID) launch_f32<S, EPI_RESID>(M, N, K, A, W, bias, e, st);
-  else if (epi == EPI_GELU) launch_f32<S, EPI_GELU>(M, N, K, A, W, bias, e, st);
-  else if (epi == EPI_QKV) launch_f32<S, EPI_QKV>(M, N, K, A, W, bias, e, st);
-}
-template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_gemm_f32<EPI_STORE>(int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_gemm_f32<EPI_RESID>(int, int, int, const float*, const void*, const void*, const EpiArgs&, hipStream_t);
 
 // LayerNorm, then the product.  One launch where the product runs 16 x 16 tiles and a wave holds
 // a row (each workgroup normalises its own 16 rows again, so larger tiles and wider rows keep
@@ -338,22 +330,21 @@ template void launch_gemm_f32<F32>(int, int, int, int, const float*, const void*
 // six row tiles only.  us a step of four layers, one launch / two: d 384, 16 rows 215 / 251, 128
 // 295 / 331, 400 633 / 648; d 512, 16 rows 245 / 269, 80 324 / 328, 96 350 / 346, 128 392 / 379,
 // 256 664 / 592.  (A model's parameters are 16-byte aligned.)
-void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
+template <int EPI>
+void launch_ln_gemm_f32(int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
                         const void* W, const void* bias, const EpiArgs& e, hipStream_t st) {
   const int MT = (M + 15) / 16, NT = (N + 15) / 16;
   if ((long long)MT * NT > 2048 || K > kRowStatsMax || (K > 384 && MT > 6)) {
     launch_layernorm<F32>(M, K, x, g, b, ln, st);
-    launch_gemm_f32<F32>(epi, M, N, K, ln, W, bias, e, st);
+    launch_gemm_f32<EPI>(M, N, K, ln, W, bias, e, st);
     return;
   }
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(NT, MT), dim3(256), 0, st, M, N, K, x, (const float*)g, (const float*)b,
-                       (const float*)W, (const float*)bias, e);
-  };
-  if (epi == EPI_STORE) go(ln_gemm_f32_kernel<F32, EPI_STORE, 3>);
-  else if (epi == EPI_GELU) go(ln_gemm_f32_kernel<F32, EPI_GELU, 3>);
-  else if (epi == EPI_QKV) go(ln_gemm_f32_kernel<F32, EPI_QKV, 3>);
+  hipLaunchKernelGGL((ln_gemm_f32_kernel<F32, EPI, 3>), dim3(NT, MT), dim3(256), 0, st, M, N, K, x, (const float*)g,
+                     (const float*)b, (const float*)W, (const float*)bias, e);
 }
+template void launch_ln_gemm_f32<EPI_STORE>(int, int, int, const float*, const void*, const void*, float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_ln_gemm_f32<EPI_GELU>(int, int, int, const float*, const void*, const void*, float*, const void*, const void*, const EpiArgs&, hipStream_t);
+template void launch_ln_gemm_f32<EPI_QKV>(int, int, int, const float*, const void*, const void*, float*, const void*, const void*, const EpiArgs&, hipStream_t);
 
 int f32_records(int N) { return (N + 63) / 64; }
 

@@ -81,20 +81,21 @@ void launch_gather_hidden(int B, int d, int layout, int k_max, const int* cu_row
 void launch_assemble_next(int B, int n_heads, int k_max, const int* accept_len, const int* out_tokens,
                           const int* head_greedy, int* next_tokens, hipStream_t st);
 
-// C = A W^T (+ bias) in float32 with the epilogue `epi` (EPI_STORE, and for float32 weights
-// EPI_RESID, EPI_GELU, EPI_QKV); A is float32 [M][K], W is [N][K] of S.
-// f32_head_argmax: `heads` products with the same A, W [heads][N][K]: per row and 64 columns a
+// C = A W^T (+ bias) in float32 with the epilogue EPI (EPI_STORE or EPI_RESID; another one does
+// not link); A is [M][K], W is [N][K], both float32.
+// f32_head_argmax: `heads` products with the same A, W [heads][N][K] of S: per row and 64 columns a
 // top-2 record, float4 am_part[heads][M][f32_records(N)] (merged by launch_argmax_final), and
 // the logits [heads][M][N] when `logits` is given.
 int f32_records(int N);
 template <class S>
 void launch_f32_head_argmax(int heads, int M, int N, int K, const float* A, const void* W, void* am_part,
                             float* logits, hipStream_t st);
-template <class S>
-void launch_gemm_f32(int epi, int M, int N, int K, const float* A, const void* W, const void* bias,
-                      const EpiArgs& e, hipStream_t st);
+template <int EPI>
+void launch_gemm_f32(int M, int N, int K, const float* A, const void* W, const void* bias, const EpiArgs& e,
+                     hipStream_t st);
 // LayerNorm of the rows x, then the product (EPI_STORE, EPI_GELU or EPI_QKV); ln holds M x K floats.
-void launch_ln_gemm_f32(int epi, int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
+template <int EPI>
+void launch_ln_gemm_f32(int M, int N, int K, const float* x, const void* g, const void* b, float* ln,
                         const void* W, const void* bias, const EpiArgs& e, hipStream_t st);
 
 // Cross-attention keys / values of a bf16 model's encoder states on the matrix cores, for
