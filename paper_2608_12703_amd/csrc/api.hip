@@ -230,7 +230,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
                  s->kv.pages_per_seq, s->kv.num_pages, s->cross.enc_len, s->cross.enc_off,
                  s->cross.frames_cap, s->cross_window, s->parents, w.tree};
   ad::launch_prep(a, w.seqs, w.rows, s->err_flag, st);
-  ad::launch_embed<ad::F32>(M, d, w.rows, m->p[P_TOK], m->p[P_POS], w.x, s->in_rows, st);
+  ad::launch_embed(M, d, w.rows, m->p[P_TOK], m->p[P_POS], w.x, s->in_rows, st);
 
   ad::EpiArgs e{};
   e.rows = w.rows;
@@ -279,7 +279,7 @@ void run_step_f32(const ad_model* m, const ad_step* s, const Workspace& w, hipSt
     copy_taps(s, l, w.x, M, d, st);
   }
   float* hidden = s->out_hidden ? s->out_hidden : w.hidden;
-  ad::launch_layernorm<ad::F32>(M, d, w.x, m->p[P_LNF_G], m->p[P_LNF_B], hidden, st);
+  ad::launch_layernorm(M, d, w.x, m->p[P_LNF_G], m->p[P_LNF_B], hidden, st);
   {
     ProfScope ps(m, AD_PROF_LM_HEAD, st);
     ad::launch_f32_head_argmax<ad::F32>(1, M, V, d, hidden, m->p[P_TOK], w.ampart, s->out_logits, st);

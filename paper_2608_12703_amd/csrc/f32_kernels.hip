@@ -335,7 +335,7 @@ void launch_ln_gemm_f32(int M, int N, int K, const float* x, const void* g, cons
                         const void* W, const void* bias, const EpiArgs& e, hipStream_t st) {
   const int MT = (M + 15) / 16, NT = (N + 15) / 16;
   if ((long long)MT * NT > 2048 || K > kRowStatsMax || (K > 384 && MT > 6)) {
-    launch_layernorm<F32>(M, K, x, g, b, ln, st);
+    launch_layernorm(M, K, x, g, b, ln, st);
     launch_gemm_f32<EPI>(M, N, K, ln, W, bias, e, st);
     return;
   }

@@ -52,11 +52,9 @@ struct EpiArgs {
 };
 
 void launch_prep(const StepArgs& a, SeqDesc* seqs, RowDesc* rows, int* err, hipStream_t st);
-// x = E_tok[token] + E_pos[pos] per row, or in_rows[row] + E_pos[pos] when in_rows is set.
-template <class S>
+// Float32 model: x = E_tok[token] + E_pos[pos] per row, or in_rows[row] + E_pos[pos] when in_rows is set.
 void launch_embed(int M, int d, const RowDesc* rows, const void* tok, const void* pos, float* x,
                   const float* in_rows, hipStream_t st);
-template <class S>
 void launch_layernorm(int M, int d, const float* x, const void* g, const void* b, float* out,
                       hipStream_t st);
 void launch_accept(int B, int k_max, const SeqDesc* seqs, const int* tokens, const int* greedy,
@@ -244,12 +242,6 @@ size_t anchor_scratch_floats(int rows, int B, int H, int max_frames);
 template <class S>
 void launch_anchor(const AnchorArgs& a, int B, hipStream_t st);
 
-// LayerNorm of float32 rows into A-fragment order (hi/lo bf16) for the next product,
-// and optionally also as float32 rows (out may be NULL).
-template <class S>
-void launch_layernorm_frag(int M, int d, const float* x, const void* g, const void* b,
-                           uint16_t* frag, int RT, float* out, hipStream_t st);
-void launch_zero_i32(int* p, int n, hipStream_t st);
 // bf16 model: x += sum of split-K partials + bias, then LayerNorm -> A fragments (and out).
 void launch_reduce_res_ln(int M, int d, int nsplit, const float* P, const void* bias, float* x,
                           const void* g, const void* b, uint16_t* frag, int RT, float* out,

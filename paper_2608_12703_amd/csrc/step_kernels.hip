@@ -111,23 +111,20 @@ __global__ void prep_row_kernel(StepArgs a, const SeqDesc* seqs, RowDesc* rows) 
 
 // ---------------------------------------------------------------- embedding
 
-template <class S>
-__global__ void embed_kernel(int d, const RowDesc* rows, const typename S::T* tok_emb,
-                             const typename S::T* pos_emb, float* x, const float* in_rows) {
+__global__ void embed_kernel(int d, const RowDesc* rows, const float* tok_emb, const float* pos_emb, float* x,
+                             const float* in_rows) {
   const int m = blockIdx.x;
   const RowDesc r = rows[m];
   for (int j = threadIdx.x; j < d; j += blockDim.x)
-    x[(size_t)m * d + j] = (in_rows ? in_rows[(size_t)m * d + j] : S::ld(tok_emb, (size_t)r.token * d + j)) +
-                           S::ld(pos_emb, (size_t)r.pos * d + j);
+    x[(size_t)m * d + j] = (in_rows ? in_rows[(size_t)m * d + j] : tok_emb[(size_t)r.token * d + j]) +
+                           pos_emb[(size_t)r.pos * d + j];
 }
 
 // ---------------------------------------------------------------- LayerNorm
 // out = (x - mean) / sqrt(var + 1e-5) * g + b, biased variance, two passes over the row.
 
-template <class S>
-__global__ void __launch_bounds__(256) layernorm_kernel(int d, const float* x,
-                                                        const typename S::T* g,
-                                                        const typename S::T* b, float* out) {
+__global__ void __launch_bounds__(256) layernorm_kernel(int d, const float* x, const float* g, const float* b,
+                                                        float* out) {
   __shared__ float red[4];
   const int m = blockIdx.x;
   const float* xr = x + (size_t)m * d;
@@ -137,7 +134,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(int d, const float* x,
     for (int t = 0; t < kRowParts; ++t) xs[t] = row_part(xr, d, threadIdx.x % 16, t);
     const float2 rs = row_stats(xs, d);
     for (int j = threadIdx.x; j < d; j += 256)
-      out[(size_t)m * d + j] = normalised(xr[j], rs, S::ld(g, j), S::ld(b, j));
+      out[(size_t)m * d + j] = normalised(xr[j], rs, g[j], b[j]);
     return;
   }
   float s = 0.f;
@@ -151,49 +148,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(int d, const float* x,
   const float var = block_sum<4>(v, red) / (float)d;
   const float rstd = 1.0f / sqrtf(var + 1e-5f);
   for (int j = threadIdx.x; j < d; j += 256)
-    out[(size_t)m * d + j] = (xr[j] - mean) * rstd * S::ld(g, j) + S::ld(b, j);
-}
-
-// Same normalisation, written as the hi/lo A operand of the next bf16 product.
-template <class S>
-__global__ void __launch_bounds__(256) layernorm_frag_kernel(int d, const float* x,
-                                                             const typename S::T* g,
-                                                             const typename S::T* b,
-                                                             uint16_t* frag, int RT, float* out) {
-  __shared__ float red[4];
-  const int m = blockIdx.x;
-  const float* xr = x + (size_t)m * d;
-  float s = 0.f;
-  for (int j = threadIdx.x; j < d; j += 256) s += xr[j];
-  const float mean = block_sum<4>(s, red) / (float)d;
-  float v = 0.f;
-  for (int j = threadIdx.x; j < d; j += 256) {
-    const float t = xr[j] - mean;
-    v += t * t;
-  }
-  const float var = block_sum<4>(v, red) / (float)d;
-  const float rstd = 1.0f / sqrtf(var + 1e-5f);
-  for (int j = threadIdx.x; j < d; j += 256) {
-    const float y = (xr[j] - mean) * rstd * S::ld(g, j) + S::ld(b, j);
-    afrag_store(frag, RT, m, j, y);
-    if (out) out[(size_t)m * d + j] = y;
-  }
-}
-
-// Split-K epilogue of the residual-writing products fused with the next LayerNorm:
-//   x[m] += sum_s P[s][m] + bias   (partials in split order)
-//   frag[m] = LN(x[m]) in A-fragment order (and, when out is given, also as float32).
-// One workgroup per row; the row is held in LDS.
-// Sum over the block's waves in wave order; every thread gets the total.
-__device__ __forceinline__ float row_block_sum(float v, float* red) {
-  v = wave_sum(v);
-  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0) red[w] = v;
-  __syncthreads();
-  float t = 0.f;
-  for (int i = 0; i < nw; ++i) t += red[i];
-  return t;
+    out[(size_t)m * d + j] = (xr[j] - mean) * rstd * g[j] + b[j];
 }
 
 // split_sum4 with the first eight planes as straight-line loads (planes past nsplit
@@ -220,8 +175,8 @@ __device__ __forceinline__ float4 split_sum4_flat(const float* P, size_t plane, 
   return acc;
 }
 
-// The same for a `red` array that no other reduction of the kernel uses (no barrier
-// needed before writing it).
+// Sum over the block's waves in wave order; every thread gets the total.  No other reduction of
+// the kernel uses `red` (no barrier before writing it).
 __device__ __forceinline__ float row_block_sum_once(float v, float* red) {
   v = wave_sum(v);
   const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
@@ -314,10 +269,6 @@ __global__ void __launch_bounds__(1024) embed_ln_kernel(int M, int d, const RowD
     afrag_store4(frag, RT, m, j,
                  float4{c.x * rstd * gv.x + bv.x, c.y * rstd * gv.y + bv.y, c.z * rstd * gv.z + bv.z,
                         c.w * rstd * gv.w + bv.w});
-}
-
-__global__ void zero_i32_kernel(int* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += blockDim.x * gridDim.x) p[i] = 0;
 }
 
 // ---------------------------------------------------------------- argmax + margin
@@ -597,31 +548,16 @@ void launch_prep(const StepArgs& a, SeqDesc* seqs, RowDesc* rows, int* err, hipS
     hipLaunchKernelGGL(prep_row_kernel, dim3((a.rows + 255) / 256), dim3(256), 0, st, a, seqs, rows);
 }
 
-template <class S>
 void launch_embed(int M, int d, const RowDesc* rows, const void* tok, const void* pos, float* x,
                   const float* in_rows, hipStream_t st) {
-  hipLaunchKernelGGL(embed_kernel<S>, dim3(M), dim3(256), 0, st, d, rows,
-                     (const typename S::T*)tok, (const typename S::T*)pos, x, in_rows);
+  hipLaunchKernelGGL(embed_kernel, dim3(M), dim3(256), 0, st, d, rows, (const float*)tok, (const float*)pos, x,
+                     in_rows);
 }
-template void launch_embed<F32>(int, int, const RowDesc*, const void*, const void*, float*, const float*, hipStream_t);
-template void launch_embed<BF16>(int, int, const RowDesc*, const void*, const void*, float*, const float*, hipStream_t);
 
-template <class S>
 void launch_layernorm(int M, int d, const float* x, const void* g, const void* b, float* out,
                       hipStream_t st) {
-  hipLaunchKernelGGL(layernorm_kernel<S>, dim3(M), dim3(256), 0, st, d, x,
-                     (const typename S::T*)g, (const typename S::T*)b, out);
+  hipLaunchKernelGGL(layernorm_kernel, dim3(M), dim3(256), 0, st, d, x, (const float*)g, (const float*)b, out);
 }
-template void launch_layernorm<F32>(int, int, const float*, const void*, const void*, float*, hipStream_t);
-template void launch_layernorm<BF16>(int, int, const float*, const void*, const void*, float*, hipStream_t);
-
-template <class S>
-void launch_layernorm_frag(int M, int d, const float* x, const void* g, const void* b,
-                           uint16_t* frag, int RT, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(layernorm_frag_kernel<S>, dim3(M), dim3(256), 0, st, d, x,
-                     (const typename S::T*)g, (const typename S::T*)b, frag, RT, out);
-}
-template void launch_layernorm_frag<BF16>(int, int, const float*, const void*, const void*, uint16_t*, int, float*, hipStream_t);
 
 void launch_reduce_res_ln(int M, int d, int nsplit, const float* P, const void* bias, float* x,
                           const void* g, const void* b, uint16_t* frag, int RT, float* out,
@@ -659,15 +595,13 @@ __global__ void draft_gather_taps_kernel(int d, int layout, int k_max, const int
 
 // z[b] = [feat[b] ; E_tok[token_b]], token_b = tokens[b * token_stride + (token_index ?
 // token_index[b] : 0)] (a negative index, i.e. a skipped sequence, reads slot 0).
-template <class S>
-__global__ void draft_concat_kernel(int d, const float* feat, const typename S::T* tok_emb,
-                                    const int* tokens, int token_stride, const int* token_index,
-                                    float* z) {
+__global__ void draft_concat_kernel(int d, const float* feat, const float* tok_emb, const int* tokens,
+                                    int token_stride, const int* token_index, float* z) {
   const int b = blockIdx.x;
   const int ti = token_index ? max(token_index[b], 0) : 0;
   const int t = max(tokens[(size_t)b * token_stride + ti], 0);
   for (int j = threadIdx.x; j < 2 * d; j += blockDim.x)
-    z[(size_t)b * 2 * d + j] = j < d ? feat[(size_t)b * d + j] : S::ld(tok_emb, (size_t)t * d + (j - d));
+    z[(size_t)b * 2 * d + j] = j < d ? feat[(size_t)b * d + j] : tok_emb[(size_t)t * d + (j - d)];
 }
 
 // window[b] = [max(0, c - half), min(T_b, c + half + 1)) around anchor c (a negative
@@ -781,7 +715,7 @@ void launch_draft_gather_taps(int B, int d, int layout, int k_max, const int* cu
 void launch_draft_concat(int B, int d, const float* feat, const void* tok_emb, const int* tokens,
                          int token_stride, const int* token_index, float* z,
                          hipStream_t st) {
-  hipLaunchKernelGGL(draft_concat_kernel<F32>, dim3(B), dim3(256), 0, st, d, feat, (const float*)tok_emb, tokens,
+  hipLaunchKernelGGL(draft_concat_kernel, dim3(B), dim3(256), 0, st, d, feat, (const float*)tok_emb, tokens,
                      token_stride, token_index, z);
 }
 
@@ -789,11 +723,6 @@ void launch_draft_window(int B, const int* anchor, const int* enc_len, int half,
                          hipStream_t st) {
   hipLaunchKernelGGL(draft_window_kernel, dim3((B + 127) / 128), dim3(128), 0, st, B, anchor,
                      enc_len, half, window);
-}
-
-void launch_zero_i32(int* p, int n, hipStream_t st) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(zero_i32_kernel, dim3(min((n + 255) / 256, 1024)), dim3(256), 0, st, p, n);
 }
 
 void launch_argmax_final(int M, int nrec, const void* part, const RowDesc* rows, int* greedy,
