@@ -101,12 +101,14 @@ void launch_ln_gemm_f32(int M, int N, int K, const float* x, const void* g, cons
 // bias[i] in the cross-K/V layout of layer first + i (N = 2d, M a multiple of 32).  a_packed:
 // enc as written by launch_pack_rows; w_packed: W tiled by launch_pack_weight; otherwise
 // row-major (row-major states: one layer).
-constexpr int kXkvLayers = 64;   // layers of one launch (1 KB of kernel arguments)
-struct XkvLayers {
-  const void* W[kXkvLayers];      // of the model's type
-  const void* bias[kXkvLayers];
+constexpr int kXkvLayers = 64;   // layers of one launch
+template <int N>
+struct XkvLayersOf {
+  const void* W[N];      // of the model's type
+  const void* bias[N];
   int first;
 };
+using XkvLayers = XkvLayersOf<kXkvLayers>;
 void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const XkvLayers& lay, int layers,
                      bool w_packed, uint16_t* cache, int H, int d, int frames_cap, hipStream_t st);
 // The same for a float32 model (row-major operands; e: the cache and its shape).

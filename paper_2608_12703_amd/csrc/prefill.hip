@@ -15,8 +15,8 @@
 //
 // Layers.  All layers that read the staged states run in one launch: one utterance has 60
 // large tiles per layer, and with a launch per layer three quarters of the chip sat idle
-// for a whole K loop 32 times (one large-v3 utterance 1770 -> 368 us), and a batch's last
-// round of workgroups was partly empty as often (16 utterances of 870 frames 3367 -> 2676 us).
+// for a whole K loop 32 times (one large-v3 utterance 1773 -> 357 us), and a batch's last
+// round of workgroups was partly empty as often (16 of 200 to 1500 frames 3278 -> 2478 us).
 //
 // Operand layouts.  Row-major operands make each 1 KB load gather 16 rows x 64 bytes,
 // which streams at a quarter of the rate of a contiguous 1 KB (measured: about 15-28
@@ -187,7 +187,8 @@ __device__ __forceinline__ void xkv_tile(int M, int N, int K, const uint16_t* A,
 
 template <int T, bool APK, bool WPK>
 __global__ void __launch_bounds__(512) xkv_mfma_kernel(int M, int N, int K, const uint16_t* A,
-                                                       XkvLayers lay, uint16_t* cache, int H, int d,
+                                                       XkvLayersOf<APK ? kXkvLayers : 1> lay,
+                                                       uint16_t* cache, int H, int d,
                                                        int frames_cap) {
   // distinct LDS objects per ring stage, so the compiler can tell a read of one stage from
   // the direct loads still filling another
@@ -236,13 +237,16 @@ static void launch_tiles(int M, int N, int K, const uint16_t* A, bool a_packed, 
                          bool w_packed, uint16_t* cache, int H, int d, int frames_cap, hipStream_t st) {
   constexpr int X = kXT * T;
   const dim3 grid(((N + X - 1) / X) * ((M + X - 1) / X) * layers), block(512);
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, block, 0, st, M, N, K, A, lay, cache, H, d, frames_cap);
+  auto go = [&](auto kernel, const auto& l) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, M, N, K, A, l, cache, H, d, frames_cap);
   };
-  if (a_packed && w_packed) go(xkv_mfma_kernel<T, true, true>);
-  else if (a_packed) go(xkv_mfma_kernel<T, true, false>);
-  else if (w_packed) go(xkv_mfma_kernel<T, false, true>);
-  else go(xkv_mfma_kernel<T, false, false>);
+  // (the 1 KB of kernel arguments of 64 layers costs a launch about 1 us: one row-major layer of
+  // d 1280, 6400 frames 41.3 us with them, 39.3 with one)
+  const XkvLayersOf<1> one{{lay.W[0]}, {lay.bias[0]}, lay.first};
+  if (a_packed && w_packed) go(xkv_mfma_kernel<T, true, true>, lay);
+  else if (a_packed) go(xkv_mfma_kernel<T, true, false>, lay);
+  else if (w_packed) go(xkv_mfma_kernel<T, false, true>, one);
+  else go(xkv_mfma_kernel<T, false, false>, one);
 }
 
 void launch_xkv_mfma(int M, int N, int K, const uint16_t* A, bool a_packed, const XkvLayers& lay, int layers,
