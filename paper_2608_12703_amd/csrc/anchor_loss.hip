@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_
 // Gradient of lambda L_anchor for the query rows (0 for rows without an alignment).
 // Four waves take interleaved 32-frame blocks, two in flight per wave (keys and the
 // row's Abar values of the block); partials merge in wave order.
-// (Three waves per SIMD, the keys' tile in the place of the later partials: 81 -> 78 us; four spill,
+// (Three waves per SIMD, the keys' tile in the place of the later partials: 81 -> 72 us; four spill,
 // 113 us.)
 __global__ void __launch_bounds__(kLossThreads) __attribute__((amdgpu_waves_per_eu(3))) aloss_dq_kernel(LossArgs a) {
   // per wave: X, Y partials [dim][row]; before that, one block's keys, [key][dim] (the partials'

@@ -434,8 +434,8 @@ __global__ void kv_copy_kernel(int L, int H, int n, int b, typename S::T* lin,
 // token-major in a tile, so their pieces move as they are, in the cache's order (128-byte runs
 // of the linear array).  Values are lane-major and are transposed through LDS.  Bound by
 // memory; the element-wise kernel spent its time on index divisions and 2-byte accesses.
-// 220 tokens of the large-v3 cache, 36 MB each way: import and export 125 -> 27 us together
-// (5.4 TB/s); 53 tokens of 30 layers x 4 heads 6.2 + 4.9 -> 3.4 + 2.9 us.
+// 220 tokens of the large-v3 cache, 36 MB each way: import and export 125 -> 31 us together
+// (4.6 TB/s; the kernels alone 13 + 12); 53 tokens of 30 layers x 4 heads 6.2 + 4.9 -> 3.4 + 2.9 us.
 // (Loads are unconditional, tokens and heads past the tile clamped, so that all of a thread's
 // are in flight together.)
 constexpr int kCopyHeads = 4;

@@ -9,7 +9,7 @@ scales with the terms, so a value near zero may lie several of its own ulps away
 below an ulp of 2^-8..2^-7 of a typical value: a value differs only when the sums
 straddle a rounding boundary.  Bar: one ulp + KV_SIGMAS EPS_OWN rms everywhere (the
 cache-value bar of the step's first layer) and at least 99.9% of the values bit-equal.
-float32 models (the VALU prefill): 1e-5 relative."""
+float32 models (float32 products and sums): 1e-5 relative."""
 import numpy as np
 import pytest
 
